@@ -107,8 +107,8 @@ typedef struct {
                               of the contribution (40: 4e-18, below FP32 resolution) */
     int32_t chunk;         /* packets per work-queue grab; 0 = default */
     int32_t waves_per_cu;  /* persistent waves per compute unit; 0 = default */
-    int32_t threshold;     /* lanes that must finish a march before events run; 0 = default
-                              (16; batches 24) */
+    int32_t threshold;     /* lanes of a wave that must finish their march before its events
+                              run; 0 = default (by the kind of launch) */
     int32_t top_level;     /* octree top-table level; -1 = default */
     int32_t brick[3];      /* Cartesian storage bricks: log2 cells per axis, summing to 5
                               (32 cells per brick); {-1, -1, -1} = chosen from the cell

@@ -18,11 +18,14 @@ template <typename Real, typename ImgT, int G> struct TransportArgs {
     View<Real, ImgT, G> view;
     const Optics<Real> *optics;   // global copies, staged into LDS by the kernel
     const InsDesc<Real> *ins;
-    uint64_t total;               // packets in this launch: n_lambda * count
     uint64_t count;               // packets per wavelength in this launch
     uint64_t first_id;            // first packet id
-    uint32_t chunk;               // packets taken per queue grab
-    int threshold;                // lanes that must finish a march before events run
+    uint64_t n_chunks;            // chunks in the work queue: n_lambda * lam_chunks
+    uint64_t lam_chunks;          // chunks of each wavelength
+    uint32_t chunk;               // packets per chunk (all of one wavelength)
+    int threshold;                // lanes that must finish their propagation before events run
+    int lanes;                    // lanes of a wave that take packets (64 but in small launches)
+    int mixed;                    // march all kinds in one loop (see transport_kernel.h)
     unsigned long long *counter;  // queue position (chunks handed out)
     double *energy;               // [4] emitted, absorbed, escaped, truncated
     unsigned long long *stats;    // [kNumStats]

@@ -33,11 +33,12 @@ using namespace mcrt;
 namespace {
 struct HostSink {
     static constexpr bool kLearn = true, kHist = true; // chosen at run time
+    static constexpr bool kDirect = false;
     void deposit(double *table, long long slab, int cell, double v)
     {
         if (v != 0.0) table[slab + cell] += v;
     }
-    template <typename L, typename T> void pixel(L &, T *images, long long idx, T v) { images[idx] += v; }
+    template <typename V, typename L, typename T> void pixel(const V &view, L &, long long idx, T v) { view.images[idx] += v; }
 };
 } // namespace
 

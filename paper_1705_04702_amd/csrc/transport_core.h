@@ -165,6 +165,15 @@ template <typename Real, typename ImgT, int G> struct View {
     // outputs
     double *table;  // [n_lambda][n_store]
     ImgT *images;   // [n_ins][n_lambda][ny][nx], flux * 4 pi d^2
+    // FP64 sums of the direct light (nullptr: it goes to the images): a point
+    // source's emission peel-offs towards an instrument all land in one pixel
+    // per wavelength.  direct[slot][shard][stride], slot = instrument *
+    // n_lambda + wavelength; direct_pix[slot]: the image element.  A pixel
+    // index of direct0 + slot names the sum.
+    double *direct;
+    long long *direct_pix;
+    long long direct0;
+    int direct_shards, direct_stride; // shards: a power of two
     // options
     Real w_min;
     long long event_cap;
@@ -200,7 +209,7 @@ template <typename Real> struct Lane {
     Real a_t0, a_tau, a_kr, a_ds; // locate: last segment with positive optical depth
     Optics<Real> opt;
     int c0, c1, c2;     // cell index (Cartesian) or lattice cursor (octree)
-    int mode, j, nseg, steps;
+    int mode, j, steps;
     long long e;
     uint32_t id, lam;
     uint32_t slot;      // packet index in the launch (histories)
@@ -208,7 +217,7 @@ template <typename Real> struct Lane {
     Real flux;          // image flux produced so far (histories)
     long long pix;      // pending pixel add (index, -1: none) for the wave-level combine
     Real pval;
-    bool marching, found, dropped, emis_dir, parked;
+    bool marching, met, found, dropped, emis_dir, parked;
 };
 
 // Per-axis fields are separate scalars (not arrays): stores through a
@@ -225,10 +234,13 @@ template <typename Real> MCRT_HD Real &tnx(Lane<Real> &ln, int a) { return a == 
 template <typename Real> struct Prec;
 template <> struct Prec<float> {
     MCRT_HD static float over_k(float num, float k, float ik) { return num * ik; }
+    // a b + c, rounded once (the form the optical depth's running sum takes)
+    MCRT_HD static float mac(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
     MCRT_HD static float inf() { return __builtin_huge_valf(); }
 };
 template <> struct Prec<double> {
     MCRT_HD static double over_k(double num, double k, double) { return num / k; }
+    MCRT_HD static double mac(double a, double b, double c) { return a * b + c; }
     MCRT_HD static double inf() { return __builtin_huge_val(); }
 };
 
@@ -380,12 +392,12 @@ MCRT_HD void begin_march(const View<Real, ImgT, G> &v, Lane<Real> &ln, const Rea
         ln.d[a] = dir[a];
         ln.id3[a] = dir[a] != Real(0) ? Real(1) / dir[a] : Real(0);
     }
-    ln.nseg = 0;
     ln.steps = 0;
     ln.tau = Real(0);
     Real t0;
     int idx[3];
     ln.marching = ray_start(v, ln.r, ln.d, t0, idx);
+    ln.met = ln.marching; // a ray that starts in the grid crosses a cell at least
     ln.c0 = idx[0];
     ln.c1 = idx[1];
     ln.c2 = idx[2];
@@ -519,29 +531,34 @@ MCRT_HD bool geo_step(const View<Real, ImgT, G> &v, Lane<Real> &ln, Tally &ty, i
     return exits;
 }
 
-// Applies one segment (cell, start, length, density) to the lane's march:
-// continuous-absorption deposit, interaction search or optical-depth sum.
-// Returns true when the march stops here (interaction found, peel-off cut).
+// Applies one propagation segment: the continuous-absorption deposit.  Written
+// for a wave whose lanes all propagate: a segment past the ray's exit (ok
+// false) is computed like the others and leaves the lane's state as it was.
 template <typename Real, typename ImgT, int G, typename Sink>
-MCRT_HD bool apply_segment(const View<Real, ImgT, G> &v, Lane<Real> &ln, Tally &ty, Sink &sink, int cell,
-                           Real t_start, Real ds, float rho)
+MCRT_HD void apply_prop(const View<Real, ImgT, G> &v, Lane<Real> &ln, Tally &ty, Sink &sink, bool ok, int cell, Real ds,
+                        float rho)
 {
-    ln.nseg++;
+    const Real kr = ln.opt.kappa * (Real)rho;
+    const Real dtau = ok ? kr * ds : Real(0);
+    ln.tau = ok ? Prec<Real>::mac(ds, kr, ln.tau) : ln.tau;
+    const Real x = -Math<Real>::e_expm1(-dtau);
+    const Real A = ok ? ln.wabs * ln.E * x : Real(0);
+    sink.deposit(v.table, (long long)ln.lam * v.n_store, cell, (double)A);
+    ty.absorbed += (double)A;
+    ln.E = ln.E * (Real(1) - x); // x = 0 where not ok
+    ty.prop_cells += ok ? 1u : 0u;
+}
+
+// Applies one segment of an interaction search or a peel-off's optical depth,
+// written as selects: the lanes of a wave mix both.  Returns true when the
+// march stops here (interaction found, peel-off cut).
+template <typename Real, typename ImgT, int G>
+MCRT_HD bool apply_scan(const View<Real, ImgT, G> &v, Lane<Real> &ln, Tally &ty, Real t_start, Real ds, float rho)
+{
     const Real kr = ln.opt.kappa * (Real)rho;
     const Real dtau = kr * ds;
     const Real tprev = ln.tau;
-    ln.tau = tprev + dtau;
-    if (ln.mode == kProp) {
-        Real x = -Math<Real>::e_expm1(-dtau);
-        Real A = ln.wabs * ln.E * x;
-        sink.deposit(v.table, (long long)ln.lam * v.n_store, cell, (double)A);
-        ty.absorbed += (double)A;
-        ln.E = ln.E * (Real(1) - x);
-        ty.prop_cells++;
-        return false;
-    }
-    // interaction search and peel-off depth, written as selects: the lanes of
-    // a wave mix both
+    ln.tau = Prec<Real>::mac(ds, kr, tprev);
     const bool loc = ln.mode == kLocate;
     const bool save = loc && dtau > Real(0); // last segment with positive depth
     ln.a_t0 = save ? t_start : ln.a_t0;
@@ -562,8 +579,10 @@ MCRT_HD bool apply_segment(const View<Real, ImgT, G> &v, Lane<Real> &ln, Tally &
 // same operations in the same order as one segment at a time).  A Cartesian
 // step is pure arithmetic, so it also runs past the ray's exit (its results
 // are not used) rather than branching; every load reads a valid cell.  An
-// octree step's walk entry carries the leaf's density.
-template <int K, typename Real, typename ImgT, int G, typename Sink>
+// octree step's walk entry carries the leaf's density.  KIND: what the wave's
+// lanes march for.
+enum MarchKind { kScans, kProps, kMixed }; // searches and peel-off depths; propagations; any
+template <MarchKind KIND, int K, typename Real, typename ImgT, int G, typename Sink>
 MCRT_HD void march_batch(const View<Real, ImgT, G> &v, Lane<Real> &ln, Tally &ty, Sink &sink)
 {
     int cell[K];
@@ -594,8 +613,14 @@ MCRT_HD void march_batch(const View<Real, ImgT, G> &v, Lane<Real> &ln, Tally &ty
     }
     bool stop = false;
 #pragma unroll
-    for (int k = 0; k < K; ++k)
-        if (ok[k] && !stop) stop = apply_segment(v, ln, ty, sink, cell[k], ts[k], ds[k], rho[k]);
+    for (int k = 0; k < K; ++k) {
+        if constexpr (KIND == kProps) {
+            apply_prop(v, ln, ty, sink, ok[k], cell[k], ds[k], rho[k]);
+        } else if (ok[k] && !stop) {
+            if (KIND == kMixed && ln.mode == kProp) apply_prop(v, ln, ty, sink, true, cell[k], ds[k], rho[k]);
+            else stop = apply_scan(v, ln, ty, ts[k], ds[k], rho[k]);
+        }
+    }
     if (stop || !more) ln.marching = false;
 }
 
@@ -608,7 +633,8 @@ template <int G> struct BatchOf {
 template <typename Real, typename ImgT, int G, typename Sink>
 MCRT_HD void march_step(const View<Real, ImgT, G> &v, Lane<Real> &ln, Tally &ty, Sink &sink)
 {
-    march_batch<BatchOf<G>::value>(v, ln, ty, sink);
+    if (ln.mode == kProp) march_batch<kProps, BatchOf<G>::value>(v, ln, ty, sink);
+    else march_batch<kScans, BatchOf<G>::value>(v, ln, ty, sink);
 }
 
 // ---------------------------------------------------------------------------
@@ -740,7 +766,6 @@ MCRT_HD void begin_peel(const View<Real, ImgT, G> &v, Lane<Real> &ln, int j, boo
             else tau = column_tau<2>(v, ln, in.col);
             ln.tau = tau;
             ln.dropped = tau >= v.tau_peel_max;
-            ln.nseg = 1;
             ln.marching = false;
         }
     } else {
@@ -752,7 +777,6 @@ MCRT_HD void begin_peel(const View<Real, ImgT, G> &v, Lane<Real> &ln, int j, boo
             else tau = octree_column_tau<2>(v, ln, in.col);
             ln.tau = tau;
             ln.dropped = tau >= v.tau_peel_max;
-            ln.nseg = 1;
             ln.marching = false;
         }
     }
@@ -1186,7 +1210,14 @@ MCRT_HD void finish_march(const View<Real, ImgT, G> &v, Lane<Real> &ln, Tally &t
             if (px >= Real(0) && px < Real(in.nx) && py >= Real(0) && py < Real(in.ny)) {
                 long long idx = in.offset + ((long long)ln.lam * in.ny + (long long)py) * in.nx + (long long)px;
                 Real val = ln.wpeel * Math<Real>::e_exp(-ln.tau);
-                sink.pixel(ln, v.images, idx, (ImgT)val);
+                if constexpr (Sink::kDirect) {
+                    if (v.direct != nullptr && ln.mode == kPeelEmit) {
+                        const long long slot = (long long)ln.j * v.n_lambda + ln.lam;
+                        v.direct_pix[slot] = idx; // every packet writes the same value
+                        idx = v.direct0 + slot;
+                    }
+                }
+                sink.pixel(v, ln, idx, (ImgT)val);
                 if (hist_on<Sink>(v)) ln.flux = ln.flux + val * in.inv4pid2;
                 ty.peel_adds++;
             }
@@ -1214,7 +1245,7 @@ MCRT_HD void finish_march(const View<Real, ImgT, G> &v, Lane<Real> &ln, Tally &t
             return;
         }
         ty.escaped += (double)esc;
-        if (ln.nseg == 0 || ln.opt.albedo == Real(0) || ln.tau == Real(0)) {
+        if (!ln.met || ln.opt.albedo == Real(0) || ln.tau == Real(0)) {
             end_packet<Sink>(v, ln);
             return;
         }
