@@ -82,6 +82,39 @@ hipError_t launch_table_readback(const double *src, double *dst, int64_t n_store
     return hipGetLastError();
 }
 
+// The copies are summed in copy order, in FP64; entries that no copy holds
+// (most of a large grid's, in a short launch) cost their reads only.  Bound
+// by those: 49 MB of copies of a 7 MB table take 18 us.
+template <typename T>
+__global__ void __launch_bounds__(256) merge_copies_kernel(T *dst, T *copies, int n, size_t elems)
+{
+    const size_t stride = (size_t)gridDim.x * blockDim.x;
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < elems; i += stride) {
+        double sum = 0.0;
+        bool any = false;
+        for (int k = 0; k < n; ++k) {
+            const T x = copies[(size_t)k * elems + i];
+            any = any || x != T(0);
+            sum += (double)x;
+        }
+        if (!any) continue;
+        for (int k = 0; k < n; ++k) copies[(size_t)k * elems + i] = T(0);
+        dst[i] = (T)((double)dst[i] + sum);
+    }
+}
+
+template <typename T>
+hipError_t launch_merge_copies(T *dst, T *copies, int n, size_t elems, hipStream_t stream)
+{
+    size_t blocks = (elems + 255) / 256;
+    if (blocks > 8192) blocks = 8192;
+    hipLaunchKernelGGL(merge_copies_kernel<T>, dim3((unsigned)blocks), dim3(256), 0, stream, dst, copies, n, elems);
+    return hipGetLastError();
+}
+
+template hipError_t launch_merge_copies<float>(float *, float *, int, size_t, hipStream_t);
+template hipError_t launch_merge_copies<double>(double *, double *, int, size_t, hipStream_t);
+
 template <typename ImgT>
 __global__ void image_scale_kernel(const ImgT *src, double *dst, int64_t n, double scale)
 {

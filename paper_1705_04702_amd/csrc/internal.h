@@ -27,6 +27,12 @@ template <typename Real, typename ImgT, int G> struct TransportArgs {
     int lanes;                    // lanes of a wave that take packets (64 but in small launches)
     int mixed;                    // march all kinds in one loop (see transport_kernel.h)
     unsigned long long *counter;  // queue position (chunks handed out)
+    // further copies of the table, [table_copies - 1][n_lambda][n_store], and
+    // of the images; workgroup b adds to copy b mod their (power-of-two) number
+    double *more_tables;
+    ImgT *more_images;
+    int table_copies, image_copies;
+    long long image_elems;
     double *energy;               // [4] emitted, absorbed, escaped, truncated
     unsigned long long *stats;    // [kNumStats]
     const void *mlp_frags;        // learned FP32: forward fragments (bf16, fragment order)
@@ -62,6 +68,9 @@ hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t stream);
 hipError_t launch_table_readback(const double *src, double *dst, int64_t n_store, int n_lambda,
                                  const int *n, const int *bs, const int *sh, const int *nb, int64_t cell0,
                                  int64_t ncell, hipStream_t stream);
+// dst[i] += the n copies' elements i (copies[n][elems]), which are cleared
+template <typename T>
+hipError_t launch_merge_copies(T *dst, T *copies, int n, size_t elems, hipStream_t stream);
 template <typename ImgT>
 hipError_t launch_image_scale(const ImgT *src, double *dst, int64_t n, double scale, hipStream_t stream);
 // Dust emission (dust.hip).  Cartesian cells in natural order

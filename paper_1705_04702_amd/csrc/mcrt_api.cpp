@@ -205,10 +205,14 @@ struct mcrt_result {
     mcrt_sim *sim = nullptr;
     double *d_table = nullptr;    // [n_lambda][n_cells]
     void *d_images = nullptr;     // float or double, [ins][lambda][y][x]
+    void *d_small = nullptr;      // the allocation of the small parts below
     // sums of direct light (see View; FP32 results of point sources; zero between launches)
     double *d_direct = nullptr;
     long long *d_direct_pix = nullptr;
     int direct_shards = 0, direct_stride = 0;
+    // further copies of the table and of the images (see copies; zero between launches)
+    double *d_more_tables = nullptr;
+    void *d_more_images = nullptr;
     double *d_energy = nullptr;   // [4]
     unsigned long long *d_stats = nullptr;   // [kNumStats]
     unsigned long long *d_counter = nullptr; // queue position
@@ -749,11 +753,9 @@ void mcrt_result_destroy(mcrt_result *res)
     (void)hipSetDevice(res->sim->ctx->device);
     dev_free(res->d_table);
     dev_free(res->d_images);
-    dev_free(res->d_direct);
-    dev_free(res->d_direct_pix);
-    dev_free(res->d_energy);
-    dev_free(res->d_stats);
-    dev_free(res->d_counter);
+    dev_free(res->d_more_tables);
+    dev_free(res->d_more_images);
+    dev_free(res->d_small);
     delete res;
 }
 
@@ -765,8 +767,7 @@ int mcrt_result_zero(mcrt_result *res)
     hipStream_t st = s->ctx->stream;
     HIP_TRY(launch_fill_zero(res->d_table, table_elems(s) * sizeof(double), st));
     HIP_TRY(launch_fill_zero(res->d_images, image_bytes(s), st));
-    HIP_TRY(launch_fill_zero(res->d_energy, 4 * sizeof(double), st));
-    HIP_TRY(launch_fill_zero(res->d_stats, kNumStats * sizeof(unsigned long long), st));
+    HIP_TRY(launch_fill_zero(res->d_energy, (4 + kNumStats) * 8, st)); // energy sums and stats
     HIP_TRY(hipStreamSynchronize(st));
     res->kernel_ms = 0.0;
     std::fill(res->seen, res->seen + kNumStats, 0ull);
@@ -783,20 +784,25 @@ int mcrt_result_create(mcrt_sim *sim, mcrt_result **out)
     r->sim = sim;
     int rc = dev_alloc((void **)&r->d_table, table_elems(sim) * sizeof(double));
     if (!rc) rc = dev_alloc(&r->d_images, image_bytes(sim));
-    if (!rc) rc = dev_alloc((void **)&r->d_energy, 4 * sizeof(double));
-    if (!rc) rc = dev_alloc((void **)&r->d_stats, kNumStats * sizeof(unsigned long long));
-    if (!rc) rc = dev_alloc((void **)&r->d_counter, sizeof(unsigned long long));
-    if (!rc && sim->opt.precision == MCRT_FP32 && sim->direct_light) {
-        // few sums: 16 shards on lines of their own, for the packets of a
-        // launch all start at once
-        const size_t slots = (size_t)sim->n_ins * (size_t)sim->medium->n_lambda;
-        r->direct_shards = slots <= 1024 ? 16 : 1;
-        r->direct_stride = slots <= 1024 ? 8 : 1;
-        const size_t bytes = slots * (size_t)(r->direct_shards * r->direct_stride) * sizeof(double);
-        rc = dev_alloc((void **)&r->d_direct, bytes);
-        if (!rc) rc = dev_alloc((void **)&r->d_direct_pix, slots * sizeof(long long));
-        if (!rc) {
-            const hipError_t e = launch_fill_zero(r->d_direct, bytes, sim->ctx->stream);
+    // one allocation for the small parts: energy sums, stats, queue position,
+    // and for FP32 results of point sources the sums of direct light -- few
+    // of those: 16 shards on lines of their own, for the packets of a launch
+    // all start at once
+    const bool direct = sim->opt.precision == MCRT_FP32 && sim->direct_light;
+    const size_t slots = direct ? (size_t)sim->n_ins * (size_t)sim->medium->n_lambda : 0;
+    r->direct_shards = slots <= 1024 ? 16 : 1;
+    r->direct_stride = slots <= 1024 ? 8 : 1;
+    const size_t head = 256, sums = slots * (size_t)(r->direct_shards * r->direct_stride) * sizeof(double);
+    static_assert((4 + kNumStats + 1) * 8 <= 256, "head of a result's small parts");
+    if (!rc) rc = dev_alloc(&r->d_small, head + sums + slots * sizeof(long long));
+    if (!rc) {
+        r->d_energy = (double *)r->d_small;
+        r->d_stats = (unsigned long long *)(r->d_energy + 4);
+        r->d_counter = r->d_stats + kNumStats;
+        if (direct) {
+            r->d_direct = (double *)((char *)r->d_small + head);
+            r->d_direct_pix = (long long *)((char *)r->d_direct + sums);
+            const hipError_t e = launch_fill_zero(r->d_direct, sums, sim->ctx->stream);
             if (e != hipSuccess) rc = fail(MCRT_EDEVICE, std::string("result_create: ") + hipGetErrorString(e));
         }
     }
@@ -824,6 +830,36 @@ static void set_direct(View<Real, ImgT, G> &v, const mcrt_sim *s, const mcrt_res
     v.direct0 = s->image_elems;
     v.direct_shards = r->direct_shards;
     v.direct_stride = r->direct_stride;
+}
+
+// Copies of an array of sums that a launch adds to (see transport_body): up
+// to eight, as long as all fit half of the 256 MB Infinity Cache (35 MB of
+// table: 10.0 ms with four copies, 10.4 with eight, 12.1 with one; 143 MB: 45.5
+// with one, 46.7 with four), and only where the packets pay for merging them,
+// about one 128-byte line each at least.
+static int copies(size_t bytes, uint64_t packets)
+{
+    int n = 8;
+    while (n > 1 && (size_t)n * bytes > (size_t(128) << 20)) n /= 2;
+    return packets >= 65536 && (uint64_t)n * bytes <= 128 * packets ? n : 1;
+}
+
+// r's further copies, allocated and cleared at their first use (kept with the
+// result); without them (no memory, or a run that may not allocate) the
+// launch goes on with one.
+template <typename T>
+static int get_copies(T **p, int n, size_t elems, bool may_alloc, hipStream_t st, int &rc)
+{
+    if (n > 1 && !*p && may_alloc) {
+        const size_t bytes = 7 * elems * sizeof(T); // as many as any launch takes
+        void *q = nullptr;
+        if (dev_alloc(&q, bytes) == MCRT_OK) {
+            const hipError_t e = launch_fill_zero(q, bytes, st);
+            if (e != hipSuccess) rc = fail(MCRT_EDEVICE, std::string("copies: ") + hipGetErrorString(e));
+            *p = (T *)q;
+        }
+    }
+    return *p ? n : 1;
 }
 
 template <typename Real, typename ImgT, int G>
@@ -917,11 +953,12 @@ static int run_impl(mcrt_sim *s, uint64_t n_per_lambda, uint64_t first_id, uint6
     const uint64_t total = count * (uint64_t)m->n_lambda;
     int wpc = s->opt.waves_per_cu > 0 ? s->opt.waves_per_cu : 16;
     uint64_t waves = (uint64_t)s->ctx->n_cu * (uint64_t)wpc;
-    // The queue's chunks: whole waves, two or more to a wave (the tail), at
-    // most 256 packets until a wave takes eight of those.
-    uint64_t auto_chunk = total / (2 * waves) / 64 * 64;
-    auto_chunk = auto_chunk < 64 ? 64 : (auto_chunk > 256 ? 256 : auto_chunk);
-    if (total / (8 * waves) > 256) auto_chunk = std::min<uint64_t>(512, total / (8 * waves) / 64 * 64);
+    // The queue's chunks: whole waves, eight or more chunks to a wave (the
+    // tail: 1.6e6 packets of a depth-9 torus take 20.1 ms in chunks of 64, 25.9
+    // in chunks of 192), at most 512 packets (1.6e7 packets of a 256^3 disk:
+    // 217 ms in chunks of 64, 210 in chunks of 512).
+    uint64_t auto_chunk = total / (8 * waves) / 64 * 64;
+    auto_chunk = auto_chunk < 64 ? 64 : (auto_chunk > 512 ? 512 : auto_chunk);
     a.threshold = s->opt.threshold > 0 ? s->opt.threshold : default_threshold(s);
     // A launch of fewer packets than lanes: every wave takes one chunk of
     // total / waves packets (55 000 packets on a 61 x 45 x 27 disk with 11
@@ -934,16 +971,18 @@ static int run_impl(mcrt_sim *s, uint64_t n_per_lambda, uint64_t first_id, uint6
         // sum it in FP64 instead, so that their number does not matter (500
         // packets in a 32^3 sphere: 0.27 ms with a lane to a wave, 0.44 with
         // 32).  Larger launches keep their images to the rounding they always
-        // had: the same shares, 32 packets or total / waves to a wave, and
-        // once waves refill their lanes, the mixed loop's refills.
+        // had: full waves (as fast there: 1e5 packets 0.66 ms with 64 or 49
+        // lanes to a wave, 0.74 with 33), and once waves refill their lanes,
+        // the mixed loop's refills.
         if (count <= 8192) {
             set_direct(v, s, r);
-        } else if (lanes < 64) {
-            lanes = std::max<uint64_t>(32, total / waves);
-        } else if (!s->prop && !hist) {
-            a.mixed = 1;
-            if (s->opt.threshold <= 0) a.threshold = 16;
-            auto_chunk = std::min<uint64_t>(256, total / waves);
+        } else {
+            lanes = 64;
+            auto_chunk = std::min<uint64_t>(256, std::max<uint64_t>(32, total / waves));
+            if (auto_chunk > 32 && !s->prop && !hist) {
+                a.mixed = 1;
+                if (s->opt.threshold <= 0) a.threshold = 16;
+            }
         }
     }
     a.lanes = lanes < 64 ? (int)lanes : 64;
@@ -952,6 +991,16 @@ static int run_impl(mcrt_sim *s, uint64_t n_per_lambda, uint64_t first_id, uint6
     a.lam_chunks = (count + a.chunk - 1) / a.chunk;
     a.n_chunks = a.lam_chunks * (uint64_t)m->n_lambda;
     a.counter = scratch ? (unsigned long long *)scratch : r->d_counter;
+    const bool point = !dust && s->source->type != kExpDisk;
+    int rc_copies = MCRT_OK;
+    a.table_copies = get_copies(&r->d_more_tables, point ? copies(table_elems(s) * sizeof(double), total) : 1,
+                                table_elems(s), !scratch, st, rc_copies);
+    a.image_copies = get_copies((ImgT **)&r->d_more_images, point ? 1 : copies(image_bytes(s), total),
+                                (size_t)s->image_elems, !scratch, st, rc_copies);
+    if (rc_copies) return rc_copies;
+    a.more_tables = r->d_more_tables;
+    a.more_images = (ImgT *)r->d_more_images;
+    a.image_elems = s->image_elems;
     a.energy = r->d_energy;
     a.stats = r->d_stats;
     if (waves > a.n_chunks) waves = a.n_chunks;
@@ -959,10 +1008,16 @@ static int run_impl(mcrt_sim *s, uint64_t n_per_lambda, uint64_t first_id, uint6
     if (grid < 1) grid = 1;
 
     auto launch = [&]() -> hipError_t {
-        if constexpr (sizeof(Real) == 4 && G == kCartesian) return launch_transport_f32c(a, grid, st);
-        else if constexpr (sizeof(Real) == 4) return launch_transport_f32o(a, grid, st);
-        else if constexpr (G == kCartesian) return launch_transport_f64c(a, grid, st);
-        else return launch_transport_f64o(a, grid, st);
+        hipError_t e;
+        if constexpr (sizeof(Real) == 4 && G == kCartesian) e = launch_transport_f32c(a, grid, st);
+        else if constexpr (sizeof(Real) == 4) e = launch_transport_f32o(a, grid, st);
+        else if constexpr (G == kCartesian) e = launch_transport_f64c(a, grid, st);
+        else e = launch_transport_f64o(a, grid, st);
+        if (e == hipSuccess && a.table_copies > 1)
+            e = launch_merge_copies(r->d_table, r->d_more_tables, a.table_copies - 1, table_elems(s), st);
+        if (e == hipSuccess && a.image_copies > 1)
+            e = launch_merge_copies((ImgT *)r->d_images, a.more_images, a.image_copies - 1, (size_t)s->image_elems, st);
+        return e;
     };
     if (scratch) {
         // no events (creating them allocates): the launch is not timed

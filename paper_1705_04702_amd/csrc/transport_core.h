@@ -531,16 +531,14 @@ MCRT_HD bool geo_step(const View<Real, ImgT, G> &v, Lane<Real> &ln, Tally &ty, i
     return exits;
 }
 
-// Applies one propagation segment: the continuous-absorption deposit.  Written
-// for a wave whose lanes all propagate: a segment past the ray's exit (ok
-// false) is computed like the others and leaves the lane's state as it was.
+// One propagation segment of optical depth dtau: the continuous-absorption
+// deposit.  Written for a wave whose lanes all propagate: a segment past the
+// ray's exit (ok false, dtau 0) is computed like the others and leaves the
+// lane's state as it was.
 template <typename Real, typename ImgT, int G, typename Sink>
-MCRT_HD void apply_prop(const View<Real, ImgT, G> &v, Lane<Real> &ln, Tally &ty, Sink &sink, bool ok, int cell, Real ds,
-                        float rho)
+MCRT_HD void apply_prop(const View<Real, ImgT, G> &v, Lane<Real> &ln, Tally &ty, Sink &sink, bool ok, int cell,
+                        Real dtau)
 {
-    const Real kr = ln.opt.kappa * (Real)rho;
-    const Real dtau = ok ? kr * ds : Real(0);
-    ln.tau = ok ? Prec<Real>::mac(ds, kr, ln.tau) : ln.tau;
     const Real x = -Math<Real>::e_expm1(-dtau);
     const Real A = ok ? ln.wabs * ln.E * x : Real(0);
     sink.deposit(v.table, (long long)ln.lam * v.n_store, cell, (double)A);
@@ -549,16 +547,14 @@ MCRT_HD void apply_prop(const View<Real, ImgT, G> &v, Lane<Real> &ln, Tally &ty,
     ty.prop_cells += ok ? 1u : 0u;
 }
 
-// Applies one segment of an interaction search or a peel-off's optical depth,
-// written as selects: the lanes of a wave mix both.  Returns true when the
-// march stops here (interaction found, peel-off cut).
+// One segment of an interaction search or a peel-off's optical depth (tprev
+// before it, ln.tau after it), written as selects: the lanes of a wave mix
+// both.  Returns true when the march stops here (interaction found, peel-off
+// cut).
 template <typename Real, typename ImgT, int G>
-MCRT_HD bool apply_scan(const View<Real, ImgT, G> &v, Lane<Real> &ln, Tally &ty, Real t_start, Real ds, float rho)
+MCRT_HD bool apply_scan(const View<Real, ImgT, G> &v, Lane<Real> &ln, Tally &ty, Real t_start, Real ds, float rho,
+                        Real kr, Real dtau, Real tprev)
 {
-    const Real kr = ln.opt.kappa * (Real)rho;
-    const Real dtau = kr * ds;
-    const Real tprev = ln.tau;
-    ln.tau = Prec<Real>::mac(ds, kr, tprev);
     const bool loc = ln.mode == kLocate;
     const bool save = loc && dtau > Real(0); // last segment with positive depth
     ln.a_t0 = save ? t_start : ln.a_t0;
@@ -614,11 +610,16 @@ MCRT_HD void march_batch(const View<Real, ImgT, G> &v, Lane<Real> &ln, Tally &ty
     bool stop = false;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
+        const Real kr = ln.opt.kappa * (Real)rho[k];
         if constexpr (KIND == kProps) {
-            apply_prop(v, ln, ty, sink, ok[k], cell[k], ds[k], rho[k]);
+            const Real dtau = ok[k] ? kr * ds[k] : Real(0);
+            ln.tau = ok[k] ? Prec<Real>::mac(ds[k], kr, ln.tau) : ln.tau;
+            apply_prop(v, ln, ty, sink, ok[k], cell[k], dtau);
         } else if (ok[k] && !stop) {
-            if (KIND == kMixed && ln.mode == kProp) apply_prop(v, ln, ty, sink, true, cell[k], ds[k], rho[k]);
-            else stop = apply_scan(v, ln, ty, ts[k], ds[k], rho[k]);
+            const Real dtau = kr * ds[k], tprev = ln.tau;
+            ln.tau = Prec<Real>::mac(ds[k], kr, tprev);
+            if (KIND == kMixed && ln.mode == kProp) apply_prop(v, ln, ty, sink, true, cell[k], dtau);
+            else stop = apply_scan(v, ln, ty, ts[k], ds[k], rho[k], kr, dtau, tprev);
         }
     }
     if (stop || !more) ln.marching = false;

@@ -297,6 +297,17 @@ __device__ __forceinline__ void transport_body(const TransportArgs<Real, ImgT, G
     __shared__ Optics<Real> s_opt[kMaxLdsLambda];
     __shared__ InsDesc<Real> s_ins[kMaxIns];
     View<Real, ImgT, G> v = a.view;
+    // Copies, for the memory side adds to one line at a time: of the table
+    // for point sources (every packet crosses the few cells around the
+    // source), of small images for extended ones (all packets share the
+    // pixels).  Workgroups are placed round-robin over the XCDs, so eight
+    // copies give each XCD its own.  1.6e6 packets in a depth-7 torus, 8
+    // wavelengths: 17.3 ms with one table, 12.8 with eight; 1e6 in a 32^3
+    // sphere: 5.8 and 4.5; disks gain nothing from copies of their tables.
+    // 2.2e6 packets of a 61 x 45 x 27 disk, 11 wavelengths, three 33^2 images:
+    // 18.5 ms in chunks of 64 with one set of images, 8.6 with eight.
+    if (const int c = blockIdx.x & (a.table_copies - 1)) v.table = a.more_tables + (c - 1) * v.n_store * v.n_lambda;
+    if (const int c = blockIdx.x & (a.image_copies - 1)) v.images = a.more_images + (c - 1) * a.image_elems;
     if (v.n_lambda <= kMaxLdsLambda) {
         for (int i = threadIdx.x; i < v.n_lambda; i += blockDim.x) s_opt[i] = a.optics[i];
         v.optics = s_opt;

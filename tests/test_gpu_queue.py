@@ -53,3 +53,32 @@ def test_direct_light(kind, packets):
     assert np.all(np.abs(a[nz] - b[nz]) <= tol * b[nz])
     assert np.allclose(ea, eb, rtol=1e-5, atol=1e-6 * eb[0])
     assert abs(ta - tb) <= 1e-5 * tb + 1e-300
+
+
+@pytest.mark.parametrize("kind", ["disk", "disk64", "octree"])
+def test_copies_merge(kind):
+    """A launch long enough for further copies of its table (point source) or
+    images (disk) equals the same packets in launches too short for them.
+    Tables: FP64 sums of the same FP32 deposits, 1e-12.  The disk's images: the
+    same FP32 values in another order; k additions to a pixel differ by at most
+    k 2^-24 of it, and its brightest pixel gets fewer than 1700 (1e-4)."""
+    if kind == "octree":
+        sc = dataclasses.replace(scene("octree"), albedo=np.full(3, 0.4))
+    else:
+        sc = scenes.disk((19, 13, 7), 3, 21)
+    n = 24_000 if kind != "disk64" else 22_500  # times 3 wavelengths: above 65536
+    ctx = mcrt.Context(0)
+    sim = mcrt.Sim(ctx, sc, mcrt.FP64_VALIDATE if kind == "disk64" else mcrt.FP32)
+    one, parts = sim.new_result(), sim.new_result()
+    for _ in range(2):  # copies are clear again after a launch
+        sim.run_into(one, n, seed=4)
+        for k in range(3):
+            sim.run_into(parts, n, seed=4, first_id=k * n // 3, count=n // 3)
+    assert {k: v for k, v in one.stats().items() if k != "kernel_ms"} == \
+        {k: v for k, v in parts.stats().items() if k != "kernel_ms"}
+    a, b = one.table(), parts.table()
+    assert np.array_equal(a != 0, b != 0) and np.allclose(a, b, rtol=1e-12, atol=0)
+    for x, y in zip(one.images(), parts.images()) if kind != "octree" else ():
+        assert np.array_equal(x != 0, y != 0) and np.allclose(x, y, rtol=1e-4, atol=0)
+    sim.close()
+    ctx.close()
