@@ -145,11 +145,14 @@ struct GradArgs {
     int random;               // 0: samples 0 .. m-1; 1: m uniform draws (with replacement) from [0, n)
     uint32_t key0, key1, step;
     float scale;              // multiplies every weight (1 / sum of the weights of the pass)
-    float *partial;           // [waves][kGradStride]
-    double *loss_partial;     // [waves]
+    float *partial;           // [workgroups][kGradStride]
+    double *loss_partial;     // [workgroups]
 };
 struct AdamArgs {
     float *theta, *m, *v;     // FP32 master parameters and moments [7400]
+    uint16_t *frags;          // packed copies of the parameters: fragments,
+    float *bias;              // biases,
+    double *theta64;          // FP64 copy
     float lr, b1, b2, eps;
     int step;                 // Adam time step (>= 1)
     int update;               // 0: only sum the gradient
@@ -163,8 +166,8 @@ hipError_t launch_proposal_pack(const float *theta, uint16_t *frags, float *bias
                                 hipStream_t stream);
 hipError_t launch_proposal_forward(const uint16_t *frags, const float *bias, const float *X, int64_t n, float *out,
                                    hipStream_t stream);
-hipError_t launch_proposal_grad(const GradArgs &g, int waves, hipStream_t stream);
-hipError_t launch_proposal_adam(const float *partial, int waves, const double *loss_partial, const AdamArgs &a,
+hipError_t launch_proposal_grad(const GradArgs &g, int groups, hipStream_t stream); // workgroups
+hipError_t launch_proposal_adam(const float *partial, int n, const double *loss_partial, const AdamArgs &a,
                                 hipStream_t stream);
 hipError_t launch_hist_count(const void *h, const void *tot, bool fp64, int64_t n_slots, int E, uint32_t *count,
                              uint64_t *offset, uint64_t *block_sums, uint64_t *total, hipStream_t st);

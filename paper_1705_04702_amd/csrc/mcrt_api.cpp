@@ -1930,12 +1930,11 @@ struct GradScratch {
     }
 };
 
-int grad_waves(const mcrt_context *ctx, int64_t m)
+// Workgroups of a gradient pass over m samples: 64 samples each, at most two
+// per compute unit, which then loop.
+int grad_groups(const mcrt_context *ctx, int64_t m)
 {
-    int64_t w = (m + 63) / 64;
-    int64_t cap = 2 * (int64_t)ctx->n_cu;
-    if (w > cap) w = cap;
-    return (int)std::max<int64_t>(w, 1);
+    return (int)std::max<int64_t>(std::min<int64_t>((m + 63) / 64, 2 * (int64_t)ctx->n_cu), 1);
 }
 
 } // namespace
@@ -2058,10 +2057,10 @@ static int grad_pass(mcrt_proposal *p, const float *dX, const float *dKP, const 
                      int random, uint64_t seed, float scale, const AdamArgs &adam_in, GradScratch &scr)
 {
     hipStream_t st = p->ctx->stream;
-    const int waves = grad_waves(p->ctx, m);
+    const int groups = grad_groups(p->ctx, m);
     if (!scr.partial) {
-        int rc = dev_alloc((void **)&scr.partial, (size_t)waves * kGradStrideFloats * sizeof(float));
-        if (!rc) rc = dev_alloc((void **)&scr.loss_partial, (size_t)waves * sizeof(double));
+        int rc = dev_alloc((void **)&scr.partial, (size_t)groups * kGradStrideFloats * sizeof(float));
+        if (!rc) rc = dev_alloc((void **)&scr.loss_partial, (size_t)groups * sizeof(double));
         if (rc) return rc;
     }
     GradArgs g{};
@@ -2079,8 +2078,8 @@ static int grad_pass(mcrt_proposal *p, const float *dX, const float *dKP, const 
     g.scale = scale;
     g.partial = scr.partial;
     g.loss_partial = scr.loss_partial;
-    HIP_TRY(launch_proposal_grad(g, waves, st));
-    HIP_TRY(launch_proposal_adam(scr.partial, waves, scr.loss_partial, adam_in, st));
+    HIP_TRY(launch_proposal_grad(g, groups, st));
+    HIP_TRY(launch_proposal_adam(scr.partial, groups, scr.loss_partial, adam_in, st));
     return MCRT_OK;
 }
 
@@ -2178,6 +2177,9 @@ int mcrt_proposal_train(mcrt_proposal *p, const mcrt_histories *h, const mcrt_tr
         a.theta = p->d_theta;
         a.m = p->d_m;
         a.v = p->d_v;
+        a.frags = p->d_frags;
+        a.bias = p->d_bias;
+        a.theta64 = p->d_theta64;
         a.lr = o.lr;
         a.b1 = o.beta1;
         a.b2 = o.beta2;
@@ -2186,10 +2188,6 @@ int mcrt_proposal_train(mcrt_proposal *p, const mcrt_histories *h, const mcrt_tr
         a.update = 1;
         a.loss_out = dL;
         rc = grad_pass(p, h->d_X, h->d_KP, h->d_C, h->n_samples, o.batch, 1, o.seed, scale, a, scr);
-        if (!rc) {
-            hipError_t e = launch_proposal_pack(p->d_theta, p->d_frags, p->d_bias, p->d_theta64, st);
-            if (e != hipSuccess) rc = fail(MCRT_EDEVICE, std::string("proposal_train: ") + hipGetErrorString(e));
-        }
     }
     double l = 0.0;
     if (!rc) {

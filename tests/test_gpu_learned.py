@@ -374,3 +374,11 @@ def test_trained_proposal_reduces_image_variance(ctx):
         sim.set_proposal(None)
         prop.close()
         sim.close()
+
+
+@pytest.mark.parametrize("n", [1, 15, 65, 2 * 256 * 64 + 17])
+def test_gradient_group_edges(ctx, n):
+    """The gradient's groups of 64 samples at their edges (a lone sample, one
+    wave's tile less one, a full group and one, more groups than workgroups),
+    with test_gradient_matches_oracle's bounds."""
+    test_gradient_matches_oracle(ctx, n)
