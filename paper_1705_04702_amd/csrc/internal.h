@@ -62,12 +62,12 @@ hipError_t launch_noalloc_setup(void *scratch_dev, const Optics<Real> *optics_ba
 
 // auxiliary kernels (aux_kernels.hip)
 hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t stream);
-// dst[(c - cell0) * n_lambda + l] = src[l * n_store + store(c)] for cells c in
-// [cell0, cell0 + ncell); store() is the bricked layout (bs, sh, nb) of a
-// Cartesian grid with n cells per axis, or the identity when bs == NULL.
+// dst[(c - c0) * n_lambda + l] = src[l * n_store + store(c)] for the n_cells
+// cells c from c0; store() is the bricked layout (bs, sh, nb) of a Cartesian
+// grid with n cells per axis, or the identity over grid_cells when bs == NULL.
 hipError_t launch_table_readback(const double *src, double *dst, int64_t n_store, int n_lambda,
-                                 const int *n, const int *bs, const int *sh, const int *nb, int64_t cell0,
-                                 int64_t ncell, hipStream_t stream);
+                                 const int *n, const int *bs, const int *sh, const int *nb, int64_t c0,
+                                 int64_t n_cells, int64_t grid_cells, hipStream_t stream);
 // dst[i] += the n copies' elements i (copies[n][elems]), which are cleared
 template <typename T>
 hipError_t launch_merge_copies(T *dst, T *copies, int n, size_t elems, hipStream_t stream);
@@ -101,9 +101,12 @@ hipError_t launch_dust_scan(double *x, long long n, int rows, double *tile_sums,
 // guide[rows][K]: first index whose running sum exceeds k (row total / K)
 hipError_t launch_dust_guide(const double *cdf, long long n, int K, int rows, int *guide, hipStream_t st);
 
-// sed[l] = scale * sum of the npix pixels of slice l (n_lambda slices)
+// sed[l] = scale * sum of the npix pixels of slice l (n_lambda slices);
+// parts: [n_lambda][sed_parts(npix)] scratch
+int64_t sed_parts(int64_t npix);
 template <typename ImgT>
-hipError_t launch_sed(const ImgT *img, double *sed, int n_lambda, int64_t npix, double scale, hipStream_t stream);
+hipError_t launch_sed(const ImgT *img, double *parts, double *sed, int n_lambda, int64_t npix, double scale,
+                      hipStream_t stream);
 
 } // namespace mcrt
 

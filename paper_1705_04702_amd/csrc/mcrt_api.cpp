@@ -65,6 +65,18 @@ void dev_free(void *p)
     if (p) (void)hipFree(p);
 }
 
+// Whether p is ordinary device memory of `device` (not host, managed or
+// another device's).
+bool on_device(const void *p, int device)
+{
+    hipPointerAttribute_t a{};
+    if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+        (void)hipGetLastError(); // unknown to the runtime: plain host memory
+        return false;
+    }
+    return a.type == hipMemoryTypeDevice && a.device == device && !a.isManaged;
+}
+
 // Owners released on every return path (HIP_TRY returns early).
 struct DevPtr {
     void *p = nullptr;
@@ -1740,6 +1752,16 @@ int mcrt_result_absorption(const mcrt_result *res, double *out, size_t count)
     const bool bricked = g->type == kCartesian;
     HIP_TRY(hipSetDevice(s->ctx->device));
     hipStream_t st = s->ctx->stream;
+    auto readback = [&](double *dst, int64_t c0, int64_t n) {
+        return launch_table_readback(res->d_table, dst, s->n_store, nl, g->n, bricked ? s->bs : nullptr, s->sh, s->nb,
+                                     c0, n, nc, st);
+    };
+    if (on_device(out, s->ctx->device)) { // the kernel writes the caller's buffer
+        hipError_t e = readback(out, 0, nc);
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        if (e != hipSuccess) return fail(MCRT_EDEVICE, std::string("result_absorption: ") + hipGetErrorString(e));
+        return MCRT_OK;
+    }
     int64_t block = std::max<int64_t>(1, ((int64_t)1 << 25) / nl); // cells per pass (<= 256 MB)
     if (block > nc) block = nc;
     double *tmp = nullptr;
@@ -1747,7 +1769,7 @@ int mcrt_result_absorption(const mcrt_result *res, double *out, size_t count)
     if (rc) return rc;
     for (int64_t c0 = 0; c0 < nc; c0 += block) {
         int64_t n = std::min(block, nc - c0);
-        hipError_t e = launch_table_readback(res->d_table, tmp, s->n_store, nl, g->n, bricked ? s->bs : nullptr, s->sh, s->nb, c0, n, st);
+        hipError_t e = readback(tmp, c0, n);
         if (e == hipSuccess)
             e = hipMemcpyAsync(out + c0 * nl, tmp, (size_t)n * nl * sizeof(double), hipMemcpyDefault, st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);
@@ -1795,13 +1817,15 @@ int mcrt_result_sed(const mcrt_result *res, int32_t ins, double *out, size_t cou
     HIP_TRY(hipSetDevice(s->ctx->device));
     hipStream_t st = s->ctx->stream;
     double *tmp = nullptr;
-    int rc = dev_alloc((void **)&tmp, (size_t)nl * sizeof(double));
+    int rc = dev_alloc((void **)&tmp, (size_t)nl * (size_t)(1 + sed_parts(npix)) * sizeof(double));
     if (rc) return rc;
     hipError_t e;
     if (s->opt.precision == MCRT_FP32)
-        e = launch_sed<float>((const float *)res->d_images + s->ins_offset[ins], tmp, nl, npix, s->inv4pid2[ins], st);
+        e = launch_sed<float>((const float *)res->d_images + s->ins_offset[ins], tmp + nl, tmp, nl, npix,
+                              s->inv4pid2[ins], st);
     else
-        e = launch_sed<double>((const double *)res->d_images + s->ins_offset[ins], tmp, nl, npix, s->inv4pid2[ins], st);
+        e = launch_sed<double>((const double *)res->d_images + s->ins_offset[ins], tmp + nl, tmp, nl, npix,
+                               s->inv4pid2[ins], st);
     if (e == hipSuccess) e = hipMemcpyAsync(out, tmp, (size_t)nl * sizeof(double), hipMemcpyDefault, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     dev_free(tmp);
