@@ -34,9 +34,9 @@ namespace {
 struct HostSink {
     static constexpr bool kLearn = true, kHist = true; // chosen at run time
     static constexpr bool kDirect = false;
-    void deposit(double *table, long long slab, int cell, double v)
+    template <typename V, typename L> void deposit(const V &view, const L &ln, int cell, double a)
     {
-        if (v != 0.0) table[slab + cell] += v;
+        if (a != 0.0) view.table[(long long)ln.lam * view.n_store + cell] += a;
     }
     template <typename V, typename L, typename T> void pixel(const V &view, L &, long long idx, T v) { view.images[idx] += v; }
 };

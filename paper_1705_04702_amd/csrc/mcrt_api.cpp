@@ -935,6 +935,7 @@ static int run_impl(mcrt_sim *s, uint64_t n_per_lambda, uint64_t first_id, uint6
     v.n_ins = s->n_ins;
     v.ins = nullptr;
     v.table = r->d_table;
+    v.wide = (uint64_t)s->n_store * (uint64_t)m->n_lambda >= (uint64_t(1) << 32);
     v.images = (ImgT *)r->d_images;
     v.w_min = (Real)s->opt.w_min;
     v.event_cap = s->opt.event_cap;
@@ -1443,6 +1444,7 @@ static int batch_impl(mcrt_sim *const *sims, int32_t n, const uint64_t *npl, uin
         v.zs = (Real)s->source->zs;
         v.n_ins = s->n_ins;
         v.table = res[i]->d_table;
+        v.wide = (uint64_t)s->n_store * (uint64_t)m->n_lambda >= (uint64_t(1) << 32);
         v.images = (ImgT *)res[i]->d_images;
         v.w_min = (Real)s->opt.w_min;
         v.event_cap = s->opt.event_cap;

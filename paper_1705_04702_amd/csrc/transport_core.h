@@ -164,6 +164,7 @@ template <typename Real, typename ImgT, int G> struct View {
     const InsDesc<Real> *ins;
     // outputs
     double *table;  // [n_lambda][n_store]
+    int wide;       // the table has 2^32 elements or more
     ImgT *images;   // [n_ins][n_lambda][ny][nx], flux * 4 pi d^2
     // FP64 sums of the direct light (nullptr: it goes to the images): a point
     // source's emission peel-offs towards an instrument all land in one pixel
@@ -539,9 +540,9 @@ template <typename Real, typename ImgT, int G, typename Sink>
 MCRT_HD void apply_prop(const View<Real, ImgT, G> &v, Lane<Real> &ln, Tally &ty, Sink &sink, bool ok, int cell,
                         Real dtau)
 {
-    const Real x = -Math<Real>::e_expm1(-dtau);
+    const Real x = -Math<Real>::e_expm1(-fabs(dtau)); // dtau >= 0: said again, for the compiler
     const Real A = ok ? ln.wabs * ln.E * x : Real(0);
-    sink.deposit(v.table, (long long)ln.lam * v.n_store, cell, (double)A);
+    sink.deposit(v, ln, cell, A);
     ty.absorbed += (double)A;
     ln.E = ln.E * (Real(1) - x); // x = 0 where not ok
     ty.prop_cells += ok ? 1u : 0u;
@@ -613,7 +614,7 @@ MCRT_HD void march_batch(const View<Real, ImgT, G> &v, Lane<Real> &ln, Tally &ty
         const Real kr = ln.opt.kappa * (Real)rho[k];
         if constexpr (KIND == kProps) {
             const Real dtau = ok[k] ? kr * ds[k] : Real(0);
-            ln.tau = ok[k] ? Prec<Real>::mac(ds[k], kr, ln.tau) : ln.tau;
+            ln.tau = rmax(dtau, ln.tau); // a propagation only asks whether it is 0
             apply_prop(v, ln, ty, sink, ok[k], cell[k], dtau);
         } else if (ok[k] && !stop) {
             const Real dtau = kr * ds[k], tprev = ln.tau;

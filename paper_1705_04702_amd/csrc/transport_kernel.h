@@ -69,38 +69,46 @@ __device__ __forceinline__ void add_pixel(const View<Real, ImgT, G> &v, long lon
 // still goes out as one request (at most TRK - K slots are held: K new
 // deposits per iteration always fit; TRK == K holds nothing).  Without held
 // runs (HOLD false) a tile of TRK >= 2 K slots lets the wave skip the flush
-// of every other iteration (see must_flush).  A slot holds the cell (u32) and
-// the FP32 absorbed luminosity, which converts to FP64 exactly.
+// of every other iteration (see must_flush).  A slot holds the table element
+// (u32; in tables of 2^32 elements and more the cell) and the FP32 absorbed
+// luminosity, which converts to FP64 exactly, side by side: one LDS access
+// each way, and an issued atomic's address is one shift and add from it.
 template <bool LEARN, bool HIST, int TRK = 0, int K = 0, bool HOLD = true, bool DIRECT = false> struct DevSink {
     static constexpr bool kLearn = LEARN, kHist = HIST, kDirect = DIRECT;
     static constexpr int kPitch = 64 + (TRK > 0 ? 64 / TRK : 0); // slot-major rows, padded
     static constexpr bool kHold = HOLD && TRK > K;
     static_assert(TRK == 0 || (64 % TRK == 0 && TRK <= 16 && TRK >= K), "slot tile");
-    uint32_t *sc = nullptr; // this lane's column of the wave's slot tiles
-    float *sv = nullptr;
-    int np = 0;        // slots in use
-    int base = 0;      // ring position of the first slot in use (kHold)
-    int run = 0;       // first slot (from base) of the open run
-    uint32_t rl = ~0u; // table line of the open run
-    __device__ __forceinline__ void deposit(double *table, long long slab, int cell, double v)
+    uint2 *slots = nullptr; // this lane's column of the wave's slot tile
+    uint32_t slab = 0;      // first table element of the lane's wavelength (0 in wide tables)
+    int np = 0;             // slots in use
+    int base = 0;           // ring position of the first slot in use (kHold)
+    int run = 0;            // first slot (from base) of the open run
+    uint32_t rl = ~0u;      // table line of the open run
+    template <typename Real, typename ImgT, int G>
+    __device__ __forceinline__ void begin(const View<Real, ImgT, G> &v, uint32_t lam)
+    {
+        if constexpr (TRK > 0) slab = v.wide ? 0u : lam * (uint32_t)v.n_store;
+    }
+    template <typename Real, typename ImgT, int G>
+    __device__ __forceinline__ void deposit(const View<Real, ImgT, G> &v, const Lane<Real> &ln, int cell, Real a)
     {
         if constexpr (TRK > 0) {
-            if (v != 0.0) {
+            if (a != Real(0)) {
+                const uint32_t elem = slab + (uint32_t)cell;
                 int slot = np;
                 if constexpr (kHold) {
-                    const uint32_t line = (uint32_t)cell >> 3;
+                    const uint32_t line = elem >> 3; // a wavelength's elements start on a line
                     if (line != rl) {
                         rl = line;
                         run = np;
                     }
                     slot = (base + np) & (TRK - 1);
                 }
-                sc[slot * kPitch] = (uint32_t)cell;
-                sv[slot * kPitch] = (float)v;
+                slots[slot * kPitch] = make_uint2(elem, __float_as_uint(a));
                 ++np;
             }
         } else {
-            if (v != 0.0) unsafeAtomicAdd(table + slab + cell, v);
+            if (a != Real(0)) unsafeAtomicAdd(v.table + ((long long)ln.lam * v.n_store + cell), (double)a);
         }
     }
     // True when some lane of the wave could overflow its slots in the next
@@ -112,8 +120,8 @@ template <bool LEARN, bool HIST, int TRK = 0, int K = 0, bool HOLD = true, bool 
     // that an issuing lane reads the words of all its rays with 128-bit loads;
     // the slots are read four rays at a time, so a flush waits on a few LDS
     // round trips.  table: the wave's table (uniform).  Whole wave active.
-    __device__ __forceinline__ void flush(int lane, bool hold, int lam, double *table, long long n_store,
-                                          const uint32_t *tile_c, const float *tile_v, uint32_t *wave_word)
+    __device__ __forceinline__ void flush(int lane, bool hold, int lam, double *table, long long n_store, int wide,
+                                          const uint2 *tile, uint32_t *wave_word)
     {
         if constexpr (TRK > 0) {
             constexpr int R = 64 / TRK;
@@ -128,8 +136,10 @@ template <bool LEARN, bool HIST, int TRK = 0, int K = 0, bool HOLD = true, bool 
             wave_lds_sync();
             const int s = lane % TRK, q = lane / TRK;
             constexpr int GW = TRK < 4 ? TRK : 4; // rays per group
+            const unsigned long long any = __ballot(lim > 0); // rays with slots to issue
 #pragma unroll
             for (int g = 0; g < TRK / GW; ++g) {
+                if ((any >> (R * GW * g)) == 0) break; // small launches use the first lanes only
                 uint32_t w[GW];
                 if constexpr (GW == 4) {
                     const uint4 x = reinterpret_cast<const uint4 *>(wave_word + q * TRK)[g];
@@ -141,21 +151,19 @@ template <bool LEARN, bool HIST, int TRK = 0, int K = 0, bool HOLD = true, bool 
 #pragma unroll
                     for (int i = 0; i < GW; ++i) w[i] = wave_word[q * TRK + GW * g + i];
                 }
-                uint32_t c[GW];
-                float a[GW];
+                uint2 x[GW];
 #pragma unroll
                 for (int i = 0; i < GW; ++i) {
-                    const int ray = R * (GW * g + i) + q;
                     const int slot = kHold ? (int)((((w[i] >> 5) & 15u) + (uint32_t)s) & (TRK - 1)) : s;
-                    c[i] = tile_c[slot * kPitch + ray];
-                    a[i] = tile_v[slot * kPitch + ray];
+                    x[i] = tile[slot * kPitch + R * (GW * g + i) + q];
                 }
 #pragma unroll
                 for (int i = 0; i < GW; ++i) {
                     if ((uint32_t)s < (w[i] & 31u)) {
-                        double *p = table + ((long long)(w[i] >> 9) * n_store + c[i]);
+                        double *p = table + (size_t)x[i].x;
+                        if (wide) p += (long long)(w[i] >> 9) * n_store;
                         __builtin_amdgcn_global_atomic_fadd_f64((__attribute__((address_space(1))) double *)p,
-                                                                (double)a[i]);
+                                                                (double)__uint_as_float(x[i].y));
                     }
                 }
             }
@@ -292,11 +300,25 @@ __device__ __forceinline__ void resolve_wave(const View<float, ImgT, G> &v, Lane
 // LEARN: learned proposal; HIST: plain run recording histories.  A variant
 // carries only the code (and registers) of its own features.
 template <typename Real, typename ImgT, int G, bool LEARN, bool HIST, bool MIX>
-__device__ __forceinline__ void transport_body(const TransportArgs<Real, ImgT, G> &a)
+__device__ __forceinline__ void transport_body()
 {
+    // The kernel's only argument, read where it is used: through a pointer
+    // whose origin is hidden at every call, so that the compiler loads the
+    // fields a phase needs with scalar loads instead of holding all of them
+    // (more than the scalar registers) across the event loop, spilled to
+    // vector registers and read back lane by lane (with slots of one LDS access
+    // and one-instruction atomic addresses, the propagation loop of 8 cells
+    // went from about 1400 to 970 VALU instructions: learned depth-7 torus 8.7 ->
+    // 8.1 ms, depth-9 torus -2 %, 1e5 packets in a 32^3 sphere -3 %).
+    typedef TransportArgs<Real, ImgT, G> Args;
+    auto A = []() -> const Args & {
+        auto p = __builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(p));
+        return *(const Args *)p;
+    };
     __shared__ Optics<Real> s_opt[kMaxLdsLambda];
     __shared__ InsDesc<Real> s_ins[kMaxIns];
-    View<Real, ImgT, G> v = a.view;
+    const Args &a = A();
     // Copies, for the memory side adds to one line at a time: of the table
     // for point sources (every packet crosses the few cells around the
     // source), of small images for extended ones (all packets share the
@@ -306,16 +328,25 @@ __device__ __forceinline__ void transport_body(const TransportArgs<Real, ImgT, G
     // sphere: 5.8 and 4.5; disks gain nothing from copies of their tables.
     // 2.2e6 packets of a 61 x 45 x 27 disk, 11 wavelengths, three 33^2 images:
     // 18.5 ms in chunks of 64 with one set of images, 8.6 with eight.
-    if (const int c = blockIdx.x & (a.table_copies - 1)) v.table = a.more_tables + (c - 1) * v.n_store * v.n_lambda;
-    if (const int c = blockIdx.x & (a.image_copies - 1)) v.images = a.more_images + (c - 1) * a.image_elems;
-    if (v.n_lambda <= kMaxLdsLambda) {
-        for (int i = threadIdx.x; i < v.n_lambda; i += blockDim.x) s_opt[i] = a.optics[i];
-        v.optics = s_opt;
-    } else {
-        v.optics = a.optics;
+    double *table = a.view.table;
+    ImgT *images = a.view.images;
+    if (const int c = blockIdx.x & (a.table_copies - 1))
+        table = a.more_tables + (c - 1) * a.view.n_store * a.view.n_lambda;
+    if (const int c = blockIdx.x & (a.image_copies - 1)) images = a.more_images + (c - 1) * a.image_elems;
+    const Optics<Real> *optics = a.optics;
+    if (a.view.n_lambda <= kMaxLdsLambda) {
+        for (int i = threadIdx.x; i < a.view.n_lambda; i += blockDim.x) s_opt[i] = optics[i];
+        optics = s_opt;
     }
-    for (int i = threadIdx.x; i < v.n_ins; i += blockDim.x) s_ins[i] = a.ins[i];
-    v.ins = s_ins;
+    for (int i = threadIdx.x; i < a.view.n_ins; i += blockDim.x) s_ins[i] = a.ins[i];
+    auto view = [&]() {
+        View<Real, ImgT, G> v = A().view;
+        v.table = table;
+        v.images = images;
+        v.optics = optics;
+        v.ins = s_ins;
+        return v;
+    };
     // learned proposal (FP32): network fragments and biases in LDS, plus a
     // feature tile [16][16] bf16 and an output tile [16][41] FP32 per wave
     constexpr bool kMfma = LEARN && sizeof(Real) == 4;
@@ -350,15 +381,13 @@ __device__ __forceinline__ void transport_body(const TransportArgs<Real, ImgT, G
     constexpr int kTR = sizeof(Real) == 4 ? (kLazy ? 2 * kK : (G == kCartesian && !LEARN ? 16 : kK)) : 0;
     typedef DevSink<LEARN, HIST, kTR, kK, !kLazy, sizeof(ImgT) == 4 && !MIX> SinkT;
     constexpr int kTile = kTR ? kTR * SinkT::kPitch : 1;
-    __shared__ uint32_t s_tc[kTR ? (kBlock / 64) * kTile : 1];
-    __shared__ float s_tv[kTR ? (kBlock / 64) * kTile : 1];
+    __shared__ uint2 s_tile[kTR ? (kBlock / 64) * kTile : 1];
     __shared__ __attribute__((aligned(16))) uint32_t s_word[kTR ? kBlock : 4];
     const int lane = __lane_id();
     const int wave = threadIdx.x >> 6;
     SinkT sink;
     if constexpr (kTR > 0) {
-        sink.sc = s_tc + wave * kTile + lane;
-        sink.sv = s_tv + wave * kTile + lane;
+        sink.slots = s_tile + wave * kTile + lane;
     }
     Lane<Real> ln;
     ln.mode = kDead;
@@ -383,6 +412,7 @@ __device__ __forceinline__ void transport_body(const TransportArgs<Real, ImgT, G
             unsigned long long dead = __ballot(free);
             if (dead == 0 || exhausted) break;
             if (cur >= end) {
+                const Args &a = A();
                 unsigned long long c = 0;
                 if (lane == 0) c = atomicAdd(a.counter, 1ull);
                 c = __shfl(c, 0, 64);
@@ -399,8 +429,11 @@ __device__ __forceinline__ void transport_body(const TransportArgs<Real, ImgT, G
             const uint32_t rank = lanes_below(dead);
             if (free && (uint64_t)rank < avail) {
                 const uint64_t i = cur + rank;
+                const auto v = view();
+                const Args &a = A();
                 launch<decltype(sink)>(v, ln, ty, (uint32_t)lam, (uint32_t)(a.first_id + i),
                                        (uint32_t)(lam * a.count + i));
+                sink.begin(v, (uint32_t)lam);
                 launched = true;
             }
             const uint64_t ndead = (uint64_t)__popcll(dead);
@@ -410,6 +443,7 @@ __device__ __forceinline__ void transport_body(const TransportArgs<Real, ImgT, G
         // every live lane has a propagation to march; with the learned
         // proposal, the lanes parked for a direction get it here
         for (;;) {
+            const auto v = view();
             if (!ln.marching && ln.mode != kDead) settle(v, ln, ty, sink);
             flush_pixels<SinkT::kDirect>(v, ln, lane, carry);
             bool again = false;
@@ -437,21 +471,23 @@ __device__ __forceinline__ void transport_body(const TransportArgs<Real, ImgT, G
 
         // propagation: every marching lane advances kK cells per iteration;
         // the iteration's deposits go out after it
+        const auto v = view();
+        const int threshold = A().threshold;
         for (;;) {
             if (ln.marching) march_batch<MIX ? kMixed : kProps, kK>(v, ln, ty, sink);
             unsigned long long waiting = __ballot(!ln.marching && (ln.mode != kDead || (slot && !exhausted)));
             unsigned long long active = __ballot(ln.marching);
-            const bool leave = active == 0 || ((MIX || !exhausted) && __popcll(waiting) >= a.threshold);
+            const bool leave = active == 0 || ((MIX || !exhausted) && __popcll(waiting) >= threshold);
             // a lane's wavelength changes only after the loop: the slots may
             // wait across iterations, never across a relaunch
             if (!kLazy || leave || sink.must_flush())
-                sink.flush(lane, ln.marching && ln.mode == kProp, (int)ln.lam, v.table, v.n_store, s_tc + wave * kTile,
-                           s_tv + wave * kTile, s_word + wave * 64);
+                sink.flush(lane, ln.marching && ln.mode == kProp, (int)ln.lam, v.table, v.n_store, v.wide,
+                           s_tile + wave * kTile, s_word + wave * 64);
             if (leave) break;
         }
     }
 
-    flush_carry<SinkT::kDirect>(v, carry, lane);
+    flush_carry<SinkT::kDirect>(view(), carry, lane);
     double e0 = wave_sum(ty.emitted), e1 = wave_sum(ty.absorbed);
     double e2 = wave_sum(ty.escaped), e3 = wave_sum(ty.truncated);
     unsigned long long s[kNumStats] = {ty.packets, ty.events, ty.prop_cells, ty.locate_cells,
@@ -460,6 +496,7 @@ __device__ __forceinline__ void transport_body(const TransportArgs<Real, ImgT, G
 #pragma unroll
     for (int i = 0; i < kNumStats; ++i) s[i] = wave_sum_u64(s[i]);
     if (lane == 0) {
+        const Args &a = A();
         unsafeAtomicAdd(&a.energy[0], e0);
         unsafeAtomicAdd(&a.energy[1], e1);
         unsafeAtomicAdd(&a.energy[2], e2);
@@ -476,16 +513,16 @@ __device__ __forceinline__ void transport_body(const TransportArgs<Real, ImgT, G
 template <int G, bool LEARN, bool HIST, bool MIX>
 __global__ void __launch_bounds__(kBlock)
 __attribute__((amdgpu_waves_per_eu(G == kOctree && !LEARN && !HIST ? 4 : 3)))
-transport_kernel_f32(TransportArgs<float, float, G> a)
+transport_kernel_f32(TransportArgs<float, float, G>)
 {
-    transport_body<float, float, G, LEARN, HIST, MIX>(a);
+    transport_body<float, float, G, LEARN, HIST, MIX>();
 }
 
 // FP64 validation kernels (the scalar FP64 network needs more registers).
 template <int G, bool LEARN, bool HIST>
-__global__ void __launch_bounds__(kBlock) transport_kernel_f64(TransportArgs<double, double, G> a)
+__global__ void __launch_bounds__(kBlock) transport_kernel_f64(TransportArgs<double, double, G>)
 {
-    transport_body<double, double, G, LEARN, HIST, false>(a);
+    transport_body<double, double, G, LEARN, HIST, false>();
 }
 
 template <typename Real, typename ImgT, int G>
@@ -532,15 +569,13 @@ __device__ __forceinline__ void batch_body(const BatchArgs<Real, ImgT> &a,
     constexpr bool kLazyB = kTR == 2 * kK;
     typedef DevSink<false, false, kTR, kK, false> SinkT;
     constexpr int kTile = kTR ? kTR * SinkT::kPitch : 1;
-    __shared__ uint32_t s_tc[kTR ? (kBlock / 64) * kTile : 1];
-    __shared__ float s_tv[kTR ? (kBlock / 64) * kTile : 1];
+    __shared__ uint2 s_tile[kTR ? (kBlock / 64) * kTile : 1];
     __shared__ __attribute__((aligned(16))) uint32_t s_word[kTR ? kBlock : 4];
     const int wave = threadIdx.x >> 6;
     const int lane = __lane_id();
     SinkT sink;
     if constexpr (kTR > 0) {
-        sink.sc = s_tc + wave * kTile + lane;
-        sink.sv = s_tv + wave * kTile + lane;
+        sink.slots = s_tile + wave * kTile + lane;
     }
     Lane<Real> ln;
     ln.mode = kDead;
@@ -612,6 +647,7 @@ __device__ __forceinline__ void batch_body(const BatchArgs<Real, ImgT> &a,
             if (ln.mode == kDead && !launched && (uint64_t)rank < avail) {
                 uint64_t P = cur + rank;
                 launch<decltype(sink)>(V(), ln, ty, (uint32_t)(P / count), (uint32_t)(first_id + P % count), (uint32_t)P);
+                sink.begin(V(), ln.lam);
                 launched = true;
             }
             uint64_t ndead = (uint64_t)__popcll(dead);
@@ -629,8 +665,8 @@ __device__ __forceinline__ void batch_body(const BatchArgs<Real, ImgT> &a,
             unsigned long long active = __ballot(ln.marching);
             const bool leave = active == 0 || __popcll(waiting) >= a.threshold;
             if (!kLazyB || leave || sink.must_flush())
-                sink.flush(lane, ln.marching && ln.mode == kProp, (int)ln.lam, V().table, V().n_store,
-                           s_tc + wave * kTile, s_tv + wave * kTile, s_word + wave * 64);
+                sink.flush(lane, ln.marching && ln.mode == kProp, (int)ln.lam, V().table, V().n_store, V().wide,
+                           s_tile + wave * kTile, s_word + wave * 64);
             if (leave) break;
         }
     }
