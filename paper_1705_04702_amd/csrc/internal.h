@@ -62,6 +62,8 @@ hipError_t launch_noalloc_setup(void *scratch_dev, const Optics<Real> *optics_ba
 
 // auxiliary kernels (aux_kernels.hip)
 hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t stream);
+// n 8-byte words from device memory to memory that a kernel can write (pinned).
+hipError_t launch_copy_words(const void *src, void *dst, size_t n, hipStream_t stream);
 // dst[(c - c0) * n_lambda + l] = src[l * n_store + store(c)] for the n_cells
 // cells c from c0; store() is the bricked layout (bs, sh, nb) of a Cartesian
 // grid with n cells per axis, or the identity over grid_cells when bs == NULL.

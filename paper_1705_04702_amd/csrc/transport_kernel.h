@@ -592,7 +592,6 @@ __device__ __forceinline__ void batch_body(const BatchArgs<Real, ImgT> &a,
     // values in registers across the event loop (a pointer carried across
     // the queue loop is not provably uniform, and its loads go to the vector
     // memory path).
-    typedef const View<Real, ImgT, 0> __attribute__((address_space(4))) CView;
     auto V = [&]() -> const View<Real, ImgT, 0> & {
         const int m = __builtin_amdgcn_readfirstlane(cur_model < 0 ? 0 : cur_model);
         return models[m].view;

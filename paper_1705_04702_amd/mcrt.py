@@ -590,24 +590,24 @@ class Proposal:
         _check(lib().mcrt_proposal_set_params(self.h, t.ctypes.data, t.size))
 
     def params(self) -> np.ndarray:
-        t = np.zeros(MLP_PARAMS, dtype=np.float32)
+        t = np.empty(MLP_PARAMS, dtype=np.float32)
         _check(lib().mcrt_proposal_get_params(self.h, t.ctypes.data, t.size))
         return t
 
     def weights_bf16(self) -> np.ndarray:
-        w = np.zeros(MLP_PARAMS, dtype=np.uint16)
+        w = np.empty(MLP_PARAMS, dtype=np.uint16)
         _check(lib().mcrt_proposal_get_weights(self.h, w.ctypes.data, w.size))
         return w
 
     def forward(self, X) -> np.ndarray:
         X = _f32(X).reshape(-1, 9)
-        out = np.zeros((X.shape[0], 40), dtype=np.float32)
+        out = np.empty((X.shape[0], 40), dtype=np.float32)
         _check(lib().mcrt_proposal_forward(self.h, X.ctypes.data, X.shape[0], out.ctypes.data))
         return out
 
     def grad(self, X, KP, C):
         X, KP, C = _f32(X).reshape(-1, 9), _f32(KP).reshape(-1, 3), _f32(C).reshape(-1)
-        g = np.zeros(MLP_PARAMS, dtype=np.float32)
+        g = np.empty(MLP_PARAMS, dtype=np.float32)
         loss = ctypes.c_double()
         _check(lib().mcrt_proposal_grad(self.h, X.ctypes.data, KP.ctypes.data, C.ctypes.data, X.shape[0],
                                         ctypes.byref(loss), g.ctypes.data))
@@ -657,16 +657,16 @@ class Histories:
         self.n_packets, self.max_events, self.n_samples, self.weight_sum = n.value, e.value, ns.value, cs.value
 
     def records(self):
-        rec = np.zeros((self.n_packets, self.max_events, 14))
-        tot = np.zeros(self.n_packets)
+        rec = np.empty((self.n_packets, self.max_events, 14))
+        tot = np.empty(self.n_packets)
         _check(lib().mcrt_histories_records(self.h, rec.ctypes.data, rec.size, tot.ctypes.data, tot.size))
         return rec, tot
 
     def samples(self):
         n = self.n_samples
-        X = np.zeros((n, 9), dtype=np.float32)
-        KP = np.zeros((n, 3), dtype=np.float32)
-        C = np.zeros(n, dtype=np.float32)
+        X = np.empty((n, 9), dtype=np.float32)
+        KP = np.empty((n, 3), dtype=np.float32)
+        C = np.empty(n, dtype=np.float32)
         if n:
             _check(lib().mcrt_histories_samples(self.h, X.ctypes.data, KP.ctypes.data, C.ctypes.data, n))
         return X, KP, C
