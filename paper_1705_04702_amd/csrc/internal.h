@@ -9,6 +9,12 @@ namespace mcrt {
 
 constexpr int kBlock = 256;    // threads per workgroup (4 waves)
 constexpr int kNumStats = 10;  // packets, events, prop, locate, peel cells, adds, dropped, capped, guard, nonfinite
+// A result's energy sums (4, FP64) and counters (kNumStats): kTallyShards shards
+// of 16 words, each on a line of its own.  Every wave adds its tally when it
+// ends, and additions to one line take turns at the memory side (7.7 ns each):
+// with one line and an instruction per word, a launch of 4096 waves spent 340 us
+// on them.
+constexpr int kTallyShards = 32, kTallyWords = 16;
 
 template <typename Real, typename ImgT, int G> struct View;
 template <typename Real> struct Optics;
@@ -25,6 +31,11 @@ template <typename Real, typename ImgT, int G> struct TransportArgs {
     uint32_t chunk;               // packets per chunk (all of one wavelength)
     int threshold;                // lanes that must finish their propagation before events run
     int lanes;                    // lanes of a wave that take packets (64 but in small launches)
+    // no more chunks than waves, all resident: a wave takes the chunk of its
+    // number (neighbouring chunks, of like cost, on different compute units),
+    // and not from the queue, whose counter is one line for all waves (8000
+    // packets in a 32^3 sphere: 567 -> 527 us)
+    int own_chunks;
     int mixed;                    // march all kinds in one loop (see transport_kernel.h)
     unsigned long long *counter;  // queue position (chunks handed out)
     // further copies of the table, [table_copies - 1][n_lambda][n_store], and
@@ -33,8 +44,7 @@ template <typename Real, typename ImgT, int G> struct TransportArgs {
     ImgT *more_images;
     int table_copies, image_copies;
     long long image_elems;
-    double *energy;               // [4] emitted, absorbed, escaped, truncated
-    unsigned long long *stats;    // [kNumStats]
+    unsigned long long *tally;    // [kTallyShards][kTallyWords]
     const void *mlp_frags;        // learned FP32: forward fragments (bf16, fragment order)
     const float *mlp_bias;        // learned FP32: biases [176]
 };
@@ -62,8 +72,15 @@ hipError_t launch_noalloc_setup(void *scratch_dev, const Optics<Real> *optics_ba
 
 // auxiliary kernels (aux_kernels.hip)
 hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t stream);
-// n 8-byte words from device memory to memory that a kernel can write (pinned).
+// The sums of a result's shards, kTallyWords words, to memory that a kernel can write.
+hipError_t launch_sum_tally(const unsigned long long *tally, unsigned long long *dst, hipStream_t stream);
 hipError_t launch_copy_words(const void *src, void *dst, size_t n, hipStream_t stream);
+// Clears three areas, each of whole 16-byte pieces but for its end.
+struct Area {
+    void *p;
+    size_t bytes;
+};
+hipError_t launch_clear(const Area (&areas)[3], hipStream_t stream);
 // dst[(c - c0) * n_lambda + l] = src[l * n_store + store(c)] for the n_cells
 // cells c from c0; store() is the bricked layout (bs, sh, nb) of a Cartesian
 // grid with n cells per axis, or the identity over grid_cells when bs == NULL.
@@ -124,8 +141,7 @@ template <typename Real, typename ImgT> struct ModelDesc {
     uint64_t first_id;
     uint64_t total;       // count * n_lambda
     uint64_t chunk0;      // index of the model's first chunk in the batch queue
-    double *energy;       // [4]
-    unsigned long long *stats; // [kNumStats]
+    unsigned long long *tally; // [kTallyShards][kTallyWords]
 };
 
 template <typename Real, typename ImgT> struct BatchArgs {

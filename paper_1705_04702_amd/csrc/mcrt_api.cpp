@@ -313,14 +313,58 @@ struct mcrt_result {
     // further copies of the table and of the images (see copies; zero between launches)
     double *d_more_tables = nullptr;
     void *d_more_images = nullptr;
-    double *d_energy = nullptr;   // [4]
-    unsigned long long *d_stats = nullptr;   // [kNumStats]
+    unsigned long long *d_tally = nullptr;   // energy sums and counters, [kTallyShards][kTallyWords]
     unsigned long long *d_counter = nullptr; // queue position
     double kernel_ms = 0.0;
     // the cumulative counters after the last launch into this result, so
     // that a launch reports (return code, run log) only what it added itself
     unsigned long long seen[kNumStats] = {};
 };
+
+constexpr size_t kTallyBytes = (size_t)kTallyShards * kTallyWords * 8;
+
+// A result's energy sums and counters on the host.
+struct HostTally {
+    double energy[4];
+    unsigned long long stats[kNumStats];
+    unsigned long long unused[kTallyWords - 4 - kNumStats];
+};
+static_assert(sizeof(HostTally) == kTallyWords * 8, "a shard's words");
+
+// From a copy of the shards, in the order of the kernel that sums them.
+static hipError_t read_tally_plain(const mcrt_result *r, HostTally &t)
+{
+    HostTally shard[kTallyShards];
+    const hipError_t e = hipMemcpy(shard, r->d_tally, sizeof(shard), hipMemcpyDeviceToHost);
+    t = HostTally{};
+    for (const HostTally &x : shard) {
+        for (int i = 0; i < 4; ++i) t.energy[i] += x.energy[i];
+        for (int i = 0; i < kNumStats; ++i) t.stats[i] += x.stats[i];
+    }
+    return e;
+}
+
+// The tallies of n results of c, with one wait for all where pinned memory has
+// room; waits for the stream.
+static hipError_t read_tallies(const mcrt_context *c, const mcrt_result *const *r, int n, HostTally *t)
+{
+    Staging::Cell cell(staging(c));
+    HostTally *pinned = cell ? (HostTally *)cell.data() : nullptr;
+    constexpr int room = (int)(Staging::kCellBytes / sizeof(HostTally));
+    hipError_t e = hipSuccess;
+    if (!pinned) e = hipStreamSynchronize(c->stream);
+    for (int i0 = 0; i0 < n && e == hipSuccess; i0 += room) {
+        const int k = n - i0 < room ? n - i0 : room;
+        for (int i = 0; i < k && e == hipSuccess; ++i)
+            e = pinned ? launch_sum_tally(r[i0 + i]->d_tally, (unsigned long long *)(pinned + i), c->stream)
+                       : read_tally_plain(r[i0 + i], t[i0 + i]);
+        if (e == hipSuccess && pinned) {
+            e = hipStreamSynchronize(c->stream);
+            if (e == hipSuccess) std::memcpy(t + i0, pinned, (size_t)k * sizeof(HostTally));
+        }
+    }
+    return e;
+}
 
 // The automatic chunk times 2^shift (at least 1, at most 2^24 packets).
 static uint64_t shifted_chunk(uint64_t c, int shift)
@@ -872,9 +916,9 @@ int mcrt_result_zero(mcrt_result *res)
     const mcrt_sim *s = res->sim;
     HIP_TRY(hipSetDevice(s->ctx->device));
     hipStream_t st = s->ctx->stream;
-    HIP_TRY(launch_fill_zero(res->d_table, table_elems(s) * sizeof(double), st));
-    HIP_TRY(launch_fill_zero(res->d_images, image_bytes(s), st));
-    HIP_TRY(launch_fill_zero(res->d_energy, (4 + kNumStats) * 8, st)); // energy sums and stats
+    HIP_TRY(launch_clear({{res->d_table, table_elems(s) * sizeof(double)},
+                          {res->d_images, image_bytes(s)},
+                          {res->d_tally, kTallyBytes}}, st));
     HIP_TRY(hipStreamSynchronize(st));
     res->kernel_ms = 0.0;
     std::fill(res->seen, res->seen + kNumStats, 0ull);
@@ -899,13 +943,11 @@ int mcrt_result_create(mcrt_sim *sim, mcrt_result **out)
     const size_t slots = direct ? (size_t)sim->n_ins * (size_t)sim->medium->n_lambda : 0;
     r->direct_shards = slots <= 1024 ? 16 : 1;
     r->direct_stride = slots <= 1024 ? 8 : 1;
-    const size_t head = 256, sums = slots * (size_t)(r->direct_shards * r->direct_stride) * sizeof(double);
-    static_assert((4 + kNumStats + 1) * 8 <= 256, "head of a result's small parts");
+    const size_t head = kTallyBytes + 256, sums = slots * (size_t)(r->direct_shards * r->direct_stride) * sizeof(double);
     if (!rc) rc = dev_alloc(&r->d_small, head + sums + slots * sizeof(long long));
     if (!rc) {
-        r->d_energy = (double *)r->d_small;
-        r->d_stats = (unsigned long long *)(r->d_energy + 4);
-        r->d_counter = r->d_stats + kNumStats;
+        r->d_tally = (unsigned long long *)r->d_small;
+        r->d_counter = r->d_tally + kTallyShards * kTallyWords;
         if (direct) {
             r->d_direct = (double *)((char *)r->d_small + head);
             r->d_direct_pix = (long long *)((char *)r->d_direct + sums);
@@ -943,12 +985,13 @@ static void set_direct(View<Real, ImgT, G> &v, const mcrt_sim *s, const mcrt_res
 // to eight, as long as all fit half of the 256 MB Infinity Cache (35 MB of
 // table: 10.0 ms with four copies, 10.4 with eight, 12.1 with one; 143 MB: 45.5
 // with one, 46.7 with four), and only where the packets pay for merging them,
-// about one 128-byte line each at least.
+// about one 128-byte line each at least (a 32^3 sphere: 30 000 packets 418 us
+// with eight copies, 448 with one; 500 packets 295 and 291).
 static int copies(size_t bytes, uint64_t packets)
 {
     int n = 8;
     while (n > 1 && (size_t)n * bytes > (size_t(128) << 20)) n /= 2;
-    return packets >= 65536 && (uint64_t)n * bytes <= 128 * packets ? n : 1;
+    return packets >= 12288 && (uint64_t)n * bytes <= 128 * packets ? n : 1;
 }
 
 // r's further copies, allocated and cleared at their first use (kept with the
@@ -1071,21 +1114,34 @@ static int run_impl(mcrt_sim *s, uint64_t n_per_lambda, uint64_t first_id, uint6
     // A launch of fewer packets than lanes: every wave takes one chunk of
     // total / waves packets (55 000 packets on a 61 x 45 x 27 disk with 11
     // wavelengths: 1.3 ms with 14 lanes to a wave, 1.4-1.5 ms with 32 or 64).
+    // On Cartesian grids as many waves as are resident (12 per compute unit),
+    // for a wave that has to wait for another one to end starts its only chunk
+    // then; point sources, whose packets all begin in the same cells, two to a
+    // SIMD while that gives a wave 32 packets at most (packets in a 32^3
+    // sphere with 16, 12 and 8 waves: 8000 540, 398 and 361 us, 32 000 654, 488
+    // and 421; on the disk, 22 000 packets 1198, 1170 and 1202, in FP64 4000 for
+    // each of 6 wavelengths 2076, 1890 and 2052).
+    const bool point = !dust && s->source->type != kExpDisk;
+    if (G == kCartesian && s->opt.waves_per_cu <= 0) {
+        uint64_t few = (uint64_t)s->ctx->n_cu * (point && total <= (uint64_t)s->ctx->n_cu * 8 * 32 ? 8 : 12);
+        if (total < 64 * few) waves = few;
+    }
     uint64_t lanes = (total + waves - 1) / waves;
     if (r->d_direct && !dust) {
         // A point source's direct light towards an instrument lands in one
         // pixel, in FP32 additions of one wave's share each, whose rounding
-        // follows their sizes.  Up to 8192 packets per wavelength the waves
+        // follows their sizes.  Up to 32768 packets per wavelength the waves
         // sum it in FP64 instead, so that their number does not matter (500
         // packets in a 32^3 sphere: 0.27 ms with a lane to a wave, 0.44 with
-        // 32).  Larger launches keep their images to the rounding they always
-        // had: full waves (as fast there: 1e5 packets 0.66 ms with 64 or 49
-        // lanes to a wave, 0.74 with 33), and once waves refill their lanes,
-        // the mixed loop's refills.
-        if (count <= 8192) {
+        // 32) and the pixel is exact.  Larger launches keep their images to the
+        // rounding they always had: full waves (as fast there: 1e5 packets
+        // 0.66 ms with 64 or 49 lanes to a wave, 0.74 with 33), and once waves
+        // refill their lanes, the mixed loop's refills.
+        if (count <= 32768) {
             set_direct(v, s, r);
         } else {
             lanes = 64;
+            waves = (uint64_t)s->ctx->n_cu * (uint64_t)wpc;
             auto_chunk = std::min<uint64_t>(256, std::max<uint64_t>(32, total / waves));
             if (auto_chunk > 32 && !s->prop && !hist) {
                 a.mixed = 1;
@@ -1099,7 +1155,6 @@ static int run_impl(mcrt_sim *s, uint64_t n_per_lambda, uint64_t first_id, uint6
     a.lam_chunks = (count + a.chunk - 1) / a.chunk;
     a.n_chunks = a.lam_chunks * (uint64_t)m->n_lambda;
     a.counter = scratch ? (unsigned long long *)scratch : r->d_counter;
-    const bool point = !dust && s->source->type != kExpDisk;
     int rc_copies = MCRT_OK;
     a.table_copies = get_copies(&r->d_more_tables, point ? copies(table_elems(s) * sizeof(double), total) : 1,
                                 table_elems(s), !scratch, st, rc_copies);
@@ -1109,9 +1164,12 @@ static int run_impl(mcrt_sim *s, uint64_t n_per_lambda, uint64_t first_id, uint6
     a.more_tables = r->d_more_tables;
     a.more_images = (ImgT *)r->d_more_images;
     a.image_elems = s->image_elems;
-    a.energy = r->d_energy;
-    a.stats = r->d_stats;
-    if (waves > a.n_chunks) waves = a.n_chunks;
+    a.tally = r->d_tally;
+    // (a wavelength's last chunk is a part, so there may be a few more of them
+    // than the waves they were made for)
+    a.own_chunks = G == kCartesian && a.n_chunks <= (uint64_t)s->ctx->n_cu * 12 &&
+                   (s->opt.waves_per_cu <= 0 || a.n_chunks <= waves);
+    if (waves > a.n_chunks || a.own_chunks) waves = a.n_chunks;
     int grid = (int)((waves + (kBlock / 64) - 1) / (kBlock / 64));
     if (grid < 1) grid = 1;
 
@@ -1127,7 +1185,7 @@ static int run_impl(mcrt_sim *s, uint64_t n_per_lambda, uint64_t first_id, uint6
             e = launch_merge_copies((ImgT *)r->d_images, a.more_images, a.image_copies - 1, (size_t)s->image_elems, st);
         return e;
     };
-    unsigned long long stats[kNumStats];
+    HostTally tally;
     if (scratch) {
         // no events (creating them allocates): the launch is not timed
         HIP_TRY(launch());
@@ -1140,14 +1198,14 @@ static int run_impl(mcrt_sim *s, uint64_t n_per_lambda, uint64_t first_id, uint6
         HIP_TRY(hipEventRecord(ev.e0, st));
         HIP_TRY(launch());
         HIP_TRY(hipEventRecord(ev.e1, st));
-        HIP_TRY(read_words(s->ctx, stats, r->d_stats, kNumStats));
+        HIP_TRY(read_tallies(s->ctx, &r, 1, &tally));
         float ms = 0.0f;
         HIP_TRY(hipEventElapsedTime(&ms, ev.e0, ev.e1));
         r->kernel_ms = ms;
     }
     Counters delta;
-    if (scratch) HIP_TRY(hipMemcpy(stats, r->d_stats, sizeof(stats), hipMemcpyDeviceToHost));
-    const int rc = launch_outcome(r, stats, delta.v);
+    if (scratch) HIP_TRY(read_tally_plain(r, tally));
+    const int rc = launch_outcome(r, tally.stats, delta.v);
     if (!scratch)
         log_launch(hist ? "proposal_collect" : (dust ? "run_dust_into" : "run_into"), &s, 1, &delta, n_per_lambda,
                    first_id, count, seed, r->kernel_ms, rc);
@@ -1552,8 +1610,7 @@ static int batch_impl(mcrt_sim *const *sims, int32_t n, const uint64_t *npl, uin
         d.first_id = 0;
         d.total = npl[i] * (uint64_t)m->n_lambda;
         d.chunk0 = chunk0;
-        d.energy = res[i]->d_energy;
-        d.stats = res[i]->d_stats;
+        d.tally = res[i]->d_tally;
         chunk0 += (d.total + chunk - 1) / chunk;
     }
     DevBlock dmd;
@@ -1582,7 +1639,8 @@ static int batch_impl(mcrt_sim *const *sims, int32_t n, const uint64_t *npl, uin
     else le = launch_batch_f64(a, grid, st);
     HIP_TRY(le);
     HIP_TRY(hipEventRecord(ev.e1, st));
-    HIP_TRY(hipEventSynchronize(ev.e1));
+    std::vector<HostTally> tallies((size_t)n);
+    HIP_TRY(read_tallies(s0->ctx, res, n, tallies.data()));
     float ms = 0.0f;
     HIP_TRY(hipEventElapsedTime(&ms, ev.e0, ev.e1));
     int worst = MCRT_OK;
@@ -1590,9 +1648,7 @@ static int batch_impl(mcrt_sim *const *sims, int32_t n, const uint64_t *npl, uin
     uint64_t requested = 0;
     for (int i = 0; i < n; ++i) {
         res[i]->kernel_ms = ms;
-        unsigned long long stt[kNumStats];
-        HIP_TRY(read_words(s0->ctx, stt, res[i]->d_stats, kNumStats));
-        const int oc = launch_outcome(res[i], stt, deltas[(size_t)i].v);
+        const int oc = launch_outcome(res[i], tallies[(size_t)i].stats, deltas[(size_t)i].v);
         if (oc == MCRT_ENONFINITE || (oc == MCRT_ELIMIT && worst == MCRT_OK)) worst = oc;
         requested += npl[i] * (uint64_t)sims[i]->medium->n_lambda;
     }
@@ -1984,8 +2040,9 @@ int mcrt_result_energy(const mcrt_result *res, double *emitted, double *absorbed
 {
     if (!res) return fail(MCRT_EINVAL, "result_energy: NULL result");
     HIP_TRY(hipSetDevice(res->sim->ctx->device));
-    double e[4];
-    HIP_TRY(read_words(res->sim->ctx, e, res->d_energy, 4));
+    HostTally t;
+    HIP_TRY(read_tallies(res->sim->ctx, &res, 1, &t));
+    const double *e = t.energy;
     if (emitted) *emitted = e[0];
     if (absorbed) *absorbed = e[1];
     if (escaped) *escaped = e[2];
@@ -1997,8 +2054,9 @@ int mcrt_result_stats(const mcrt_result *res, mcrt_stats *stats)
 {
     if (!res || !stats) return fail(MCRT_EINVAL, "result_stats: NULL argument");
     HIP_TRY(hipSetDevice(res->sim->ctx->device));
-    unsigned long long s[kNumStats];
-    HIP_TRY(read_words(res->sim->ctx, s, res->d_stats, kNumStats));
+    HostTally t;
+    HIP_TRY(read_tallies(res->sim->ctx, &res, 1, &t));
+    const unsigned long long *s = t.stats;
     stats->packets = s[0];
     stats->events = s[1];
     stats->prop_cells = s[2];

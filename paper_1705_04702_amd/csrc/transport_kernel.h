@@ -257,6 +257,28 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long x)
     return x;
 }
 
+// Adds the wave's tally to a shard of the result's (see kTallyShards) and
+// clears it: the words side by side in lanes, so that all energy sums and all
+// counters are one request each.  Whole wave active.
+__device__ __forceinline__ void add_tally(Tally &ty, unsigned long long *tally, int lane)
+{
+    const double e0 = wave_sum(ty.emitted), e1 = wave_sum(ty.absorbed);
+    const double e2 = wave_sum(ty.escaped), e3 = wave_sum(ty.truncated);
+    const uint32_t s[kNumStats] = {ty.packets, ty.events, ty.prop_cells, ty.locate_cells, ty.peel_cells,
+                                   ty.peel_adds, ty.peel_dropped, ty.capped, ty.guard, ty.nonfinite};
+    unsigned long long n = 0;
+#pragma unroll
+    for (int i = 0; i < kNumStats; ++i) {
+        const unsigned long long x = wave_sum_u64(s[i]);
+        n = lane == 4 + i ? x : n;
+    }
+    const double e = lane == 0 ? e0 : (lane == 1 ? e1 : (lane == 2 ? e2 : e3));
+    unsigned long long *p = tally + (size_t)(blockIdx.x % kTallyShards) * kTallyWords + lane;
+    if (lane < 4) unsafeAtomicAdd((double *)p, e);
+    else if (n) atomicAdd(p, n);
+    ty = Tally{};
+}
+
 // Learned proposal, FP32: the lanes waiting for a direction are ranked
 // (mbcnt over the ballot) and evaluated 16 at a time on the matrix cores;
 // their features go through a per-wave LDS tile into the B operand, the 40
@@ -400,7 +422,7 @@ __device__ __forceinline__ void transport_body()
     carry_init(carry, lane);
     uint64_t cur = 0, end = 0; // the wave's chunk: ids [cur, end) of wavelength lam
     int lam = 0;
-    bool exhausted = false;
+    bool exhausted = false, took = false;
     const bool slot = lane < a.lanes;
 
     for (;;) {
@@ -413,9 +435,14 @@ __device__ __forceinline__ void transport_body()
             if (dead == 0 || exhausted) break;
             if (cur >= end) {
                 const Args &a = A();
-                unsigned long long c = 0;
-                if (lane == 0) c = atomicAdd(a.counter, 1ull);
-                c = __shfl(c, 0, 64);
+                unsigned long long c = (uint64_t)(threadIdx.x >> 6) * gridDim.x + blockIdx.x;
+                if (a.own_chunks) {
+                    if (took) c = a.n_chunks;
+                } else {
+                    if (lane == 0) c = atomicAdd(a.counter, 1ull);
+                    c = __shfl(c, 0, 64);
+                }
+                took = true;
                 if (c >= a.n_chunks) {
                     exhausted = true;
                     break;
@@ -488,23 +515,7 @@ __device__ __forceinline__ void transport_body()
     }
 
     flush_carry<SinkT::kDirect>(view(), carry, lane);
-    double e0 = wave_sum(ty.emitted), e1 = wave_sum(ty.absorbed);
-    double e2 = wave_sum(ty.escaped), e3 = wave_sum(ty.truncated);
-    unsigned long long s[kNumStats] = {ty.packets, ty.events, ty.prop_cells, ty.locate_cells,
-                                       ty.peel_cells, ty.peel_adds, ty.peel_dropped, ty.capped,
-                                       ty.guard, ty.nonfinite};
-#pragma unroll
-    for (int i = 0; i < kNumStats; ++i) s[i] = wave_sum_u64(s[i]);
-    if (lane == 0) {
-        const Args &a = A();
-        unsafeAtomicAdd(&a.energy[0], e0);
-        unsafeAtomicAdd(&a.energy[1], e1);
-        unsafeAtomicAdd(&a.energy[2], e2);
-        unsafeAtomicAdd(&a.energy[3], e3);
-#pragma unroll
-        for (int i = 0; i < kNumStats; ++i)
-            if (s[i]) atomicAdd(&a.stats[i], s[i]);
-    }
+    add_tally(ty, A().tally, lane);
 }
 
 // FP32 production kernels: at most 168 VGPRs, three waves per SIMD; the
@@ -523,28 +534,6 @@ template <int G, bool LEARN, bool HIST>
 __global__ void __launch_bounds__(kBlock) transport_kernel_f64(TransportArgs<double, double, G>)
 {
     transport_body<double, double, G, LEARN, HIST, false>();
-}
-
-template <typename Real, typename ImgT, int G>
-__device__ __forceinline__ void flush_tally(Tally &ty, double *energy, unsigned long long *stats, int lane)
-{
-    double e0 = wave_sum(ty.emitted), e1 = wave_sum(ty.absorbed);
-    double e2 = wave_sum(ty.escaped), e3 = wave_sum(ty.truncated);
-    unsigned long long s[kNumStats] = {ty.packets, ty.events, ty.prop_cells, ty.locate_cells,
-                                       ty.peel_cells, ty.peel_adds, ty.peel_dropped, ty.capped,
-                                       ty.guard, ty.nonfinite};
-#pragma unroll
-    for (int i = 0; i < kNumStats; ++i) s[i] = wave_sum_u64(s[i]);
-    if (lane == 0) {
-        unsafeAtomicAdd(&energy[0], e0);
-        unsafeAtomicAdd(&energy[1], e1);
-        unsafeAtomicAdd(&energy[2], e2);
-        unsafeAtomicAdd(&energy[3], e3);
-#pragma unroll
-        for (int i = 0; i < kNumStats; ++i)
-            if (s[i]) atomicAdd(&stats[i], s[i]);
-    }
-    ty = Tally{};
 }
 
 // Batched launch over many Cartesian models (the many-small-models use case
@@ -629,7 +618,7 @@ __device__ __forceinline__ void batch_body(const BatchArgs<Real, ImgT> &a,
                     if (__ballot(ln.mode != kDead) != 0) break; // drain before switching
                     if (cur_model >= 0) {
                         flush_carry<false>(V(), carry, lane);
-                        flush_tally<Real, ImgT, 0>(ty, a.models[cur_model].energy, a.models[cur_model].stats, lane);
+                        add_tally(ty, a.models[cur_model].tally, lane);
                     }
                     cur_model = pend_model;
                     const ModelDesc<Real, ImgT> &m = a.models[cur_model];
@@ -671,7 +660,7 @@ __device__ __forceinline__ void batch_body(const BatchArgs<Real, ImgT> &a,
     }
     if (cur_model >= 0) {
         flush_carry<false>(V(), carry, lane);
-        flush_tally<Real, ImgT, 0>(ty, a.models[cur_model].energy, a.models[cur_model].stats, lane);
+        add_tally(ty, a.models[cur_model].tally, lane);
     }
 }
 
