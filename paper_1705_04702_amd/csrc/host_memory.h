@@ -93,7 +93,7 @@ class DevicePool {
         void *p;
         size_t cap;
     };
-    static constexpr size_t kIdleBlocks = 32, kIdleBytes = size_t(256) << 20;
+    static constexpr size_t kIdleBlocks = 32, kIdleBytes = size_t(1) << 30;
 
     bool drain()
     {

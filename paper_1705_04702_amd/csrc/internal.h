@@ -182,7 +182,9 @@ struct AdamArgs {
 };
 constexpr int kGradStrideFloats = 7424;
 constexpr int kFragAllElems = 60 * 64 * 4; // bf16 values of all fragments
-hipError_t launch_sum_f32(const float *x, int64_t n, double *out, hipStream_t stream);
+hipError_t launch_sum_f32(const float *x, int64_t n, double *cols, double *out, hipStream_t stream); // cols [1024]
+// Tiles of records that the compaction counts and scans.
+int64_t hist_tiles(int64_t n_slots, int E);
 hipError_t launch_proposal_pack(const float *theta, uint16_t *frags, float *bias, double *theta64,
                                 hipStream_t stream);
 hipError_t launch_proposal_forward(const uint16_t *frags, const float *bias, const float *X, int64_t n, float *out,

@@ -2474,13 +2474,13 @@ int mcrt_proposal_collect(mcrt_sim *sim, uint64_t n_per_lambda, uint64_t first_i
     // compaction into training samples
     DevBlock b_count, b_off, b_bs;
     if (!rc) {
-        const int64_t nb = ((int64_t)npk + 1023) / 1024;
-        rc = b_count.alloc(pool, (size_t)npk * sizeof(uint32_t));
-        if (!rc) rc = b_off.alloc(pool, (size_t)npk * sizeof(uint64_t));
-        if (!rc) rc = b_bs.alloc(pool, (size_t)(nb + 2) * sizeof(uint64_t)); // and the two totals
+        const int64_t tiles = hist_tiles((int64_t)npk, max_events), nb = (tiles + 1023) / 1024;
+        rc = b_count.alloc(pool, (size_t)tiles * sizeof(uint32_t));
+        if (!rc) rc = b_off.alloc(pool, (size_t)tiles * sizeof(uint64_t));
+        if (!rc) rc = b_bs.alloc(pool, (size_t)(nb + 2 + 1024) * sizeof(uint64_t)); // the two totals, 1024 columns
     }
     uint32_t *d_count = b_count.as<uint32_t>();
-    uint64_t *d_off = b_off.as<uint64_t>(), *d_tot = b_bs.as<uint64_t>(), *d_bs = d_tot + 2;
+    uint64_t *d_off = b_off.as<uint64_t>(), *d_tot = b_bs.as<uint64_t>(), *d_bs = d_tot + 2 + 1024;
     double *d_csum = (double *)(d_tot + 1);
     if (!rc) {
         uint64_t ns = 0;
@@ -2499,7 +2499,7 @@ int mcrt_proposal_collect(mcrt_sim *sim, uint64_t n_per_lambda, uint64_t first_i
             if (!rc) {
                 e = launch_hist_write(h->d_hist, h->d_total, h->fp64, (int64_t)npk, max_events, d_off, h->d_X,
                                       h->d_KP, h->d_C, st);
-                if (e == hipSuccess) e = launch_sum_f32(h->d_C, (int64_t)ns, d_csum, st);
+                if (e == hipSuccess) e = launch_sum_f32(h->d_C, (int64_t)ns, d_csum + 1, d_csum, st);
                 if (e == hipSuccess) e = read_words(sim->ctx, &h->c_sum, d_csum, 1);
                 if (e != hipSuccess) rc = fail(MCRT_EDEVICE, std::string("proposal_collect: ") + hipGetErrorString(e));
             }
