@@ -141,6 +141,8 @@ template <typename Real, typename ImgT> struct ModelDesc {
     uint64_t first_id;
     uint64_t total;       // count * n_lambda
     uint64_t chunk0;      // index of the model's first chunk in the batch queue
+    uint32_t chunk;       // packets per chunk
+    int apart;            // one kind of march per loop from the start (see the batch kernel)
     unsigned long long *tally; // [kTallyShards][kTallyWords]
 };
 
@@ -148,7 +150,7 @@ template <typename Real, typename ImgT> struct BatchArgs {
     const ModelDesc<Real, ImgT> *models;
     int n_models;
     uint64_t total_chunks;
-    uint32_t chunk;
+    int drain;            // the kernel for few chunks
     int threshold;
     unsigned long long *counter;
 };

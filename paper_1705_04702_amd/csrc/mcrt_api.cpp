@@ -1535,6 +1535,12 @@ static int batch_impl(mcrt_sim *const *sims, int32_t n, const uint64_t *npl, uin
     auto_chunk = auto_chunk < 256 ? 256 : (auto_chunk > 16384 ? 16384 : auto_chunk);
     const uint32_t chunk =
         (uint32_t)(s0->opt.chunk > 0 ? (uint64_t)s0->opt.chunk : shifted_chunk(auto_chunk, s0->opt.chunk_shift));
+    // FP32 models of few packets per wavelength take smaller chunks, which
+    // spread the batch over two waves per SIMD, 64 packets to a wave at most
+    // (see the batch kernel for both rules).
+    const uint64_t few = sizeof(Real) == 4 && s0->opt.chunk <= 0 && s0->opt.chunk_shift == 0 ? 3072 : 0;
+    const uint64_t spread = total_packets / (8ull * (uint64_t)s0->ctx->n_cu);
+    const uint32_t few_chunk = (uint32_t)(spread < 4 ? 4 : (spread > 64 ? 64 : spread));
     // Queue order: by estimated cost (packets x wavelengths x cells along the
     // axes) the most and least expensive alternating (default: on a batch of
     // 256 uneven models 1.5 % faster than longest-processing-time order and
@@ -1611,7 +1617,9 @@ static int batch_impl(mcrt_sim *const *sims, int32_t n, const uint64_t *npl, uin
         d.total = npl[i] * (uint64_t)m->n_lambda;
         d.chunk0 = chunk0;
         d.tally = res[i]->d_tally;
-        chunk0 += (d.total + chunk - 1) / chunk;
+        d.apart = npl[i] <= few;
+        d.chunk = d.apart ? few_chunk : chunk;
+        chunk0 += (d.total + d.chunk - 1) / d.chunk;
     }
     DevBlock dmd;
     int rc = dmd.alloc(s0->ctx->pool, md.size() * sizeof(ModelDesc<Real, ImgT>));
@@ -1622,7 +1630,7 @@ static int batch_impl(mcrt_sim *const *sims, int32_t n, const uint64_t *npl, uin
     a.models = (const ModelDesc<Real, ImgT> *)dmd.p;
     a.n_models = n;
     a.total_chunks = chunk0;
-    a.chunk = chunk;
+    a.drain = chunk0 <= 24ull * (uint64_t)s0->ctx->n_cu; // up to 1.5 chunks to a wave; at 3 both are as fast
     a.threshold = s0->opt.threshold > 0 ? s0->opt.threshold : 24;
     a.counter = res[0]->d_counter;
     int wpc = s0->opt.waves_per_cu > 0 ? s0->opt.waves_per_cu : 16;

@@ -13,7 +13,10 @@ hipError_t launch_transport_f32o(const TransportArgs<float, float, 1> &a, int gr
 }
 hipError_t launch_batch_f32(const BatchArgs<float, float> &a, int grid, hipStream_t stream, int slots)
 {
-    if (slots == 8) return launch_batch_impl<float, float, 8>(a, grid, stream);
-    return launch_batch_impl<float, float, 16>(a, grid, stream);
+    if (a.drain)
+        return slots == 8 ? launch_batch_impl<float, float, 8, true>(a, grid, stream)
+                          : launch_batch_impl<float, float, 16, true>(a, grid, stream);
+    return slots == 8 ? launch_batch_impl<float, float, 8, false>(a, grid, stream)
+                      : launch_batch_impl<float, float, 16, false>(a, grid, stream);
 }
 } // namespace mcrt
