@@ -36,6 +36,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <climits>
+
 #define MCRT_HD __device__ __forceinline__
 #include "transport_core.h"
 #include "internal.h"
@@ -257,6 +259,199 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long x)
     return x;
 }
 
+// Lane `src`'s value, in scalar registers.
+__device__ __forceinline__ int lane_value(int x, int src) { return __builtin_amdgcn_readlane(x, src); }
+__device__ __forceinline__ float lane_value(float x, int src)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), src));
+}
+__device__ __forceinline__ double lane_value(double x, int src)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), src),
+                            __builtin_amdgcn_readlane(__double2loint(x), src));
+}
+
+// x to lane `to` (each lane that matters to another one).
+__device__ __forceinline__ int push_value(int x, int to) { return __builtin_amdgcn_ds_permute(to << 2, x); }
+__device__ __forceinline__ float push_value(float x, int to)
+{
+    return __int_as_float(__builtin_amdgcn_ds_permute(to << 2, __float_as_int(x)));
+}
+__device__ __forceinline__ double push_value(double x, int to)
+{
+    return __hiloint2double(__builtin_amdgcn_ds_permute(to << 2, __double2hiint(x)),
+                            __builtin_amdgcn_ds_permute(to << 2, __double2loint(x)));
+}
+
+// Lane 0's march on a Cartesian grid, to its end, by the whole wave, for
+// launches of one packet to a wave: an iteration of the march loops costs as much
+// for one lane as for 64 (about 130 vector instructions per cell, of which a wave
+// alone on its SIMD issues one in four cycles).  The wave takes 21 to 61 cells
+// at a time instead:
+//   * lane 21 a + m takes crossing m of axis a (the ray parameter of a plane
+//     follows from the plane's number alone) and finds its rank among all
+//     three axes' crossings: an estimate from the position, made exact by
+//     comparing the planes next to it, ties in axis order as geo_step takes
+//     them;
+//   * the crossings move to the lanes of their ranks, which load their cells'
+//     densities together and take their optical depths and exponentials;
+//   * what is a chain -- the running luminosity, the running optical depth -- is
+//     multiplied or summed through lane by lane, in the order of the cells.
+// Every value is computed by the operations of march_batch, so deposits,
+// interaction points and depths are bit for bit the same.  Kernel of 500 packets
+// in a 32^3 sphere 285 -> 227 us, of 220 on a 61 x 45 x 27 disk 830 -> 665 us (what
+// remains is the events, about 2500 vector instructions each); with more than one
+// packet to a wave, marched one after another, nothing is gained (4000 in the
+// sphere, two to a wave: 316 and 327 us), and 1e5 there lose 5 % to the registers.
+// PROP: a propagation, else a search or a peel-off.  Whole wave active.
+// A march that cannot go on this way (no finite crossing) stays with lane 0.
+template <bool PROP, typename Real, typename ImgT, int G>
+__device__ __forceinline__ void lone_march(const View<Real, ImgT, G> &v, Lane<Real> &ln, Tally &ty, int lane)
+{
+    constexpr int src = 0;
+    if (!__builtin_amdgcn_readfirstlane(ln.marching ? 1 : 0)) return;
+    constexpr int M = 21; // crossings per axis
+    Real r[3], d[3], id[3];
+    int c[3], u[3], s[3];
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+        r[b] = lane_value(ln.r[b], src);
+        d[b] = lane_value(ln.d[b], src);
+        id[b] = lane_value(ln.id3[b], src);
+        c[b] = lane_value(cidx(ln, b), src);
+        u[b] = d[b] > Real(0) ? 1 : 0;
+        s[b] = 2 * u[b] - 1;
+    }
+    Real t = lane_value(ln.t, src);
+    const Real kappa = lane_value(ln.opt.kappa, src), wabs = lane_value(ln.wabs, src);
+    const bool loc = !PROP && lane_value(ln.mode, src) == kLocate;
+    const Real limit = loc ? lane_value(ln.tau_int, src) : v.tau_peel_max;
+    Real E = lane_value(ln.E, src), tau = lane_value(ln.tau, src);
+    const long long slab = (long long)lane_value((int)ln.lam, src) * v.n_store;
+    const int ax = lane >= 2 * M ? 2 : (lane >= M ? 1 : 0), m = lane - M * ax;
+    auto crossing = [&](int b, int k) -> Real { // of plane k along the ray on axis b
+        const Real x = Prec<Real>::over_k(v.lo[b] + (Real)(c[b] + u[b] + s[b] * k) * v.cs[b] - r[b], d[b], id[b]);
+        return d[b] != Real(0) ? x : Prec<Real>::inf();
+    };
+    bool done = false;
+    while (!done) {
+        Real T = crossing(0, m);
+        T = ax == 1 ? crossing(1, m) : T;
+        T = ax == 2 ? crossing(2, m) : T;
+        bool valid = m < M && T < Prec<Real>::inf();
+        int n[3]; // crossings of each axis before this one
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+            auto before = [&](int k) {
+                const Real x = crossing(b, k);
+                return x < T || (x == T && b < ax);
+            };
+            int k = s[b] * ((int)((r[b] + T * d[b] - v.lo[b]) * v.ics[b]) - c[b]);
+            k = k < 0 ? 0 : (k > M ? M : k);
+            const bool look = valid && ax != b && d[b] != Real(0);
+            while (look && k > 0 && !before(k - 1)) --k;
+            while (look && k < M && before(k)) ++k;
+            n[b] = ax == b ? m : (look ? k : 0);
+            valid = valid && n[b] < M;
+        }
+        const unsigned long long all = __ballot(valid);
+        int count = __popcll(all);
+        if (count == 0) break;
+        const int rank = valid ? n[0] + n[1] + n[2] : 63; // ranks stay below 61
+        const int x0 = c[0] + s[0] * n[0], x1 = c[1] + s[1] * n[1], x2 = c[2] + s[2] * n[2];
+        const int next = ax == 0 ? x0 + s[0] : (ax == 1 ? x1 + s[1] : x2 + s[2]);
+        const int size = ax == 0 ? v.n[0] : (ax == 1 ? v.n[1] : v.n[2]);
+        const int to = push_value(store_index(v, x0, x1, x2) | ((unsigned)next >= (unsigned)size ? INT_MIN : 0), rank);
+        const Real te = rmax(push_value(T, rank), t);
+        Real ts = __shfl_up(te, 1, 64);
+        ts = lane == 0 ? t : ts;
+        const unsigned long long ex = __ballot(lane < count && to < 0);
+        done = ex != 0;
+        t = lane_value(te, count - 1);
+        count = done ? __ffsll((long long)ex) : count;
+        bool ok = lane < count;
+        const Real ds = ok ? te - ts : Real(0);
+        const float rho = gload(v.density, ok ? to & 0x7fffffff : 0);
+        const Real kr = ok ? kappa * (Real)rho : Real(0);
+        const Real dtau = ok ? kr * ds : Real(0);
+        if constexpr (PROP) {
+            const Real x = -Math<Real>::e_expm1(-fabs(dtau));
+            const Real f = Real(1) - x; // 1 where not ok
+            Real El = E;
+            for (int k = 0; k < count; k += 8) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    El = lane == k + i ? E : El;
+                    E = E * lane_value(f, k + i);
+                }
+            }
+            const Real A = ok ? wabs * El * x : Real(0);
+            if (A != Real(0))
+                __builtin_amdgcn_global_atomic_fadd_f64(
+                    (__attribute__((address_space(1))) double *)(v.table + (slab + (to & 0x7fffffff))), (double)A);
+            ty.absorbed += (double)A;
+            ty.prop_cells += ok ? 1u : 0u;
+            const unsigned long long some = __ballot(dtau > Real(0));
+            if (some) tau = rmax(lane_value(dtau, __ffsll((long long)some) - 1), tau); // asked only whether it is 0
+        } else {
+            Real tl = tau;
+            int k = 0;
+            for (; k < count; k += 8) {
+                if (k > 0 && __builtin_amdgcn_readfirstlane(tau >= limit ? 1 : 0)) break; // the cells after a hit do not matter
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    tl = lane == k + i ? tau : tl;
+                    tau = Prec<Real>::mac(lane_value(ds, k + i), lane_value(kr, k + i), tau);
+                }
+            }
+            count = k < count ? k : count;
+            const Real ta = Prec<Real>::mac(ds, kr, tl);
+            const unsigned long long hits = __ballot(lane < count && ta >= limit);
+            if (hits) count = __ffsll((long long)hits);
+            tau = lane_value(ta, count - 1);
+            ok = lane < count;
+            const unsigned long long deep = __ballot(ok && dtau > Real(0));
+            if (loc && deep) { // last segment with positive depth
+                const int l = 63 - __clzll((long long)deep);
+                const Real a0 = lane_value(ts, l), a1 = lane_value(tl, l), a2 = lane_value(kr, l),
+                           a3 = lane_value(ds, l), a4 = (Real)lane_value(rho, l);
+                if (lane == src) {
+                    ln.a_t0 = a0;
+                    ln.a_tau = a1;
+                    ln.a_kr = a2;
+                    ln.a_ds = a3;
+                    ln.rho_star = a4;
+                }
+            }
+            ty.locate_cells += ok && loc ? 1u : 0u;
+            ty.peel_cells += ok && !loc ? 1u : 0u;
+            if (hits) {
+                done = true;
+                if (lane == src) {
+                    ln.found = ln.found || loc;
+                    ln.dropped = ln.dropped || !loc;
+                }
+            }
+        }
+#pragma unroll
+        for (int b = 0; b < 3; ++b) c[b] += s[b] * (int)__popcll(all >> (M * b) & ((1ull << M) - 1));
+    }
+    if (lane == src) {
+        ln.E = E;
+        ln.tau = tau;
+        ln.t = t;
+        ln.c0 = c[0];
+        ln.c1 = c[1];
+        ln.c2 = c[2];
+        ln.marching = !done;
+        if (!done) {
+            ln.tn0 = next_plane_t(v, ln, 0);
+            ln.tn1 = next_plane_t(v, ln, 1);
+            ln.tn2 = next_plane_t(v, ln, 2);
+        }
+    }
+}
+
 // Adds the wave's tally to a shard of the result's (see kTallyShards) and
 // clears it: the words side by side in lanes, so that all energy sums and all
 // counters are one request each.  Whole wave active.
@@ -321,7 +516,7 @@ __device__ __forceinline__ void resolve_wave(const View<float, ImgT, G> &v, Lane
 
 // LEARN: learned proposal; HIST: plain run recording histories.  A variant
 // carries only the code (and registers) of its own features.
-template <typename Real, typename ImgT, int G, bool LEARN, bool HIST, bool MIX>
+template <typename Real, typename ImgT, int G, bool LEARN, bool HIST, bool MIX, bool LONE>
 __device__ __forceinline__ void transport_body()
 {
     // The kernel's only argument, read where it is used: through a pointer
@@ -486,6 +681,7 @@ __device__ __forceinline__ void transport_body()
             if constexpr (!MIX) {
                 while (__ballot(ln.marching && ln.mode != kProp) != 0) {
                     again = true;
+                    if constexpr (LONE) lone_march<false>(v, ln, ty, lane);
                     if (ln.marching && ln.mode != kProp) march_batch<kScans, kK>(v, ln, ty, sink);
                 }
             }
@@ -501,6 +697,7 @@ __device__ __forceinline__ void transport_body()
         const auto v = view();
         const int threshold = A().threshold;
         for (;;) {
+            if constexpr (LONE) lone_march<true>(v, ln, ty, lane);
             if (ln.marching) march_batch<MIX ? kMixed : kProps, kK>(v, ln, ty, sink);
             unsigned long long waiting = __ballot(!ln.marching && (ln.mode != kDead || (slot && !exhausted)));
             unsigned long long active = __ballot(ln.marching);
@@ -521,19 +718,19 @@ __device__ __forceinline__ void transport_body()
 // FP32 production kernels: at most 168 VGPRs, three waves per SIMD; the
 // plain octree kernel, bound by the latency of its walk's dependent loads,
 // four waves per SIMD (128 VGPRs, a few registers spilled).
-template <int G, bool LEARN, bool HIST, bool MIX>
+template <int G, bool LEARN, bool HIST, bool MIX, bool LONE = false>
 __global__ void __launch_bounds__(kBlock)
-__attribute__((amdgpu_waves_per_eu(G == kOctree && !LEARN && !HIST ? 4 : 3)))
+__attribute__((amdgpu_waves_per_eu(G == kOctree && !LEARN && !HIST ? 4 : (LONE ? 2 : 3))))
 transport_kernel_f32(TransportArgs<float, float, G>)
 {
-    transport_body<float, float, G, LEARN, HIST, MIX>();
+    transport_body<float, float, G, LEARN, HIST, MIX, LONE>();
 }
 
 // FP64 validation kernels (the scalar FP64 network needs more registers).
-template <int G, bool LEARN, bool HIST>
+template <int G, bool LEARN, bool HIST, bool LONE = false>
 __global__ void __launch_bounds__(kBlock) transport_kernel_f64(TransportArgs<double, double, G>)
 {
-    transport_body<double, double, G, LEARN, HIST, false>();
+    transport_body<double, double, G, LEARN, HIST, false, LONE>();
 }
 
 // Batched launch over many Cartesian models (the many-small-models use case
@@ -752,6 +949,8 @@ hipError_t launch_transport_impl(const TransportArgs<Real, ImgT, G> &a, int grid
             hipLaunchKernelGGL((transport_kernel_f32<G, false, true, false>), dim3(grid), dim3(kBlock), 0, stream, a);
         else if (a.mixed)
             hipLaunchKernelGGL((transport_kernel_f32<G, false, false, true>), dim3(grid), dim3(kBlock), 0, stream, a);
+        else if (G == kCartesian && a.lanes == 1)
+            hipLaunchKernelGGL((transport_kernel_f32<G, false, false, false, G == kCartesian>), dim3(grid), dim3(kBlock), 0, stream, a);
         else
             hipLaunchKernelGGL((transport_kernel_f32<G, false, false, false>), dim3(grid), dim3(kBlock), 0, stream, a);
         if (a.view.direct) {
@@ -771,6 +970,8 @@ hipError_t launch_transport_impl(const TransportArgs<Real, ImgT, G> &a, int grid
             hipLaunchKernelGGL((transport_kernel_f64<G, true, false>), dim3(grid), dim3(kBlock), 0, stream, a);
         else if (a.view.hist)
             hipLaunchKernelGGL((transport_kernel_f64<G, false, true>), dim3(grid), dim3(kBlock), 0, stream, a);
+        else if (G == kCartesian && a.lanes == 1)
+            hipLaunchKernelGGL((transport_kernel_f64<G, false, false, G == kCartesian>), dim3(grid), dim3(kBlock), 0, stream, a);
         else
             hipLaunchKernelGGL((transport_kernel_f64<G, false, false>), dim3(grid), dim3(kBlock), 0, stream, a);
     }
