@@ -26,6 +26,7 @@ using std::sqrt;
 
 #define MCRT_HD inline
 #include "transport_core.h"
+#include "launch_plan.h"
 #include "scene_setup.h"
 
 using namespace mcrt;
@@ -254,4 +255,15 @@ extern "C" int ls_run(const ls_scene *s, uint64_t n_per_lambda, uint64_t first_i
     }
     if (s->precision == 1) return run<double, kCartesian>(s, n_per_lambda, first_id, count, seed, out);
     return run<float, kCartesian>(s, n_per_lambda, first_id, count, seed, out);
+}
+
+// The launch rules (launch_plan.h): in the fields of LaunchIn, out those of LaunchPlan.
+extern "C" void ls_plan(const int64_t in[11], int64_t out[10])
+{
+    const LaunchIn x{(uint64_t)in[0], (uint64_t)in[1], (uint64_t)in[2], in[3] != 0, in[4] != 0, in[5] != 0, in[6] != 0,
+                     (int)in[7], (int)in[8], (int)in[9], (int)in[10]};
+    const LaunchPlan p = plan_launch(x);
+    const int64_t y[10] = {(int64_t)p.waves, p.chunk, (int64_t)p.lam_chunks, (int64_t)p.n_chunks, p.lanes, p.threshold,
+                          p.mixed, p.sums, p.own_chunks, p.copies};
+    for (int i = 0; i < 10; ++i) out[i] = y[i];
 }

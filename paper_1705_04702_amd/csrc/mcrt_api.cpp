@@ -21,6 +21,7 @@
 #include "transport_core.h"
 #include "host_memory.h"
 #include "internal.h"
+#include "launch_plan.h"
 #include "scene_setup.h"
 
 using namespace mcrt;
@@ -364,13 +365,6 @@ static hipError_t read_tallies(const mcrt_context *c, const mcrt_result *const *
         }
     }
     return e;
-}
-
-// The automatic chunk times 2^shift (at least 1, at most 2^24 packets).
-static uint64_t shifted_chunk(uint64_t c, int shift)
-{
-    c = shift >= 0 ? c << shift : c >> (-shift);
-    return c < 1 ? 1 : (c > (uint64_t(1) << 24) ? (uint64_t(1) << 24) : c);
 }
 
 // Codes after which a launch's results are still there to use.
@@ -966,9 +960,12 @@ int mcrt_result_create(mcrt_sim *sim, mcrt_result **out)
     return MCRT_OK;
 }
 
-// Lanes of a wave that must finish their propagation before its events run
-// (see transport_kernel.h).
-static int default_threshold(const mcrt_sim *s) { return s->medium->grid->type == kOctree ? 48 : 64; }
+// What the launch rules look at, for count packets per wavelength of s.
+static LaunchIn launch_in(const mcrt_sim *s, uint64_t count, bool point, bool direct, bool no_hist)
+{
+    return {(uint64_t)s->ctx->n_cu, count, (uint64_t)s->medium->n_lambda, s->medium->grid->type == kOctree, point,
+            direct, !s->prop && no_hist, s->opt.chunk, s->opt.chunk_shift, s->opt.waves_per_cu, s->opt.threshold};
+}
 
 // The launch sums its direct light in r's FP64 sums.
 template <typename Real, typename ImgT, int G>
@@ -1102,61 +1099,19 @@ static int run_impl(mcrt_sim *s, uint64_t n_per_lambda, uint64_t first_id, uint6
     a.count = count;
     a.first_id = first_id;
     const uint64_t total = count * (uint64_t)m->n_lambda;
-    int wpc = s->opt.waves_per_cu > 0 ? s->opt.waves_per_cu : 16;
-    uint64_t waves = (uint64_t)s->ctx->n_cu * (uint64_t)wpc;
-    // The queue's chunks: whole waves, eight or more chunks to a wave (the
-    // tail: 1.6e6 packets of a depth-9 torus take 20.1 ms in chunks of 64, 25.9
-    // in chunks of 192), at most 512 packets (1.6e7 packets of a 256^3 disk:
-    // 217 ms in chunks of 64, 210 in chunks of 512).
-    uint64_t auto_chunk = total / (8 * waves) / 64 * 64;
-    auto_chunk = auto_chunk < 64 ? 64 : (auto_chunk > 512 ? 512 : auto_chunk);
-    a.threshold = s->opt.threshold > 0 ? s->opt.threshold : default_threshold(s);
-    // A launch of fewer packets than lanes: every wave takes one chunk of
-    // total / waves packets (55 000 packets on a 61 x 45 x 27 disk with 11
-    // wavelengths: 1.3 ms with 14 lanes to a wave, 1.4-1.5 ms with 32 or 64).
-    // On Cartesian grids as many waves as are resident (12 per compute unit),
-    // for a wave that has to wait for another one to end starts its only chunk
-    // then; point sources, whose packets all begin in the same cells, two to a
-    // SIMD while that gives a wave 32 packets at most (packets in a 32^3
-    // sphere with 16, 12 and 8 waves: 8000 540, 398 and 361 us, 32 000 654, 488
-    // and 421; on the disk, 22 000 packets 1198, 1170 and 1202, in FP64 4000 for
-    // each of 6 wavelengths 2076, 1890 and 2052).
     const bool point = !dust && s->source->type != kExpDisk;
-    if (G == kCartesian && s->opt.waves_per_cu <= 0) {
-        uint64_t few = (uint64_t)s->ctx->n_cu * (point && total <= (uint64_t)s->ctx->n_cu * 8 * 32 ? 8 : 12);
-        if (total < 64 * few) waves = few;
-    }
-    uint64_t lanes = (total + waves - 1) / waves;
-    if (r->d_direct && !dust) {
-        // A point source's direct light towards an instrument lands in one
-        // pixel, in FP32 additions of one wave's share each, whose rounding
-        // follows their sizes.  Up to 32768 packets per wavelength the waves
-        // sum it in FP64 instead, so that their number does not matter (500
-        // packets in a 32^3 sphere: 0.27 ms with a lane to a wave, 0.44 with
-        // 32) and the pixel is exact.  Larger launches keep their images to the
-        // rounding they always had: full waves (as fast there: 1e5 packets
-        // 0.66 ms with 64 or 49 lanes to a wave, 0.74 with 33), and once waves
-        // refill their lanes, the mixed loop's refills.
-        if (count <= 32768) {
-            set_direct(v, s, r);
-        } else {
-            lanes = 64;
-            waves = (uint64_t)s->ctx->n_cu * (uint64_t)wpc;
-            auto_chunk = std::min<uint64_t>(256, std::max<uint64_t>(32, total / waves));
-            if (auto_chunk > 32 && !s->prop && !hist) {
-                a.mixed = 1;
-                if (s->opt.threshold <= 0) a.threshold = 16;
-            }
-        }
-    }
-    a.lanes = lanes < 64 ? (int)lanes : 64;
-    if (a.lanes < 64) auto_chunk = (uint64_t)a.lanes;
-    a.chunk = (uint32_t)(s->opt.chunk > 0 ? (uint64_t)s->opt.chunk : shifted_chunk(auto_chunk, s->opt.chunk_shift));
-    a.lam_chunks = (count + a.chunk - 1) / a.chunk;
-    a.n_chunks = a.lam_chunks * (uint64_t)m->n_lambda;
+    const LaunchPlan plan = plan_launch(launch_in(s, count, point, r->d_direct && !dust, !hist));
+    if (plan.sums) set_direct(v, s, r);
+    a.threshold = plan.threshold;
+    a.lanes = plan.lanes;
+    a.chunk = plan.chunk;
+    a.lam_chunks = plan.lam_chunks;
+    a.n_chunks = plan.n_chunks;
+    a.own_chunks = plan.own_chunks;
+    a.mixed = plan.mixed;
     a.counter = scratch ? (unsigned long long *)scratch : r->d_counter;
     int rc_copies = MCRT_OK;
-    a.table_copies = get_copies(&r->d_more_tables, point ? copies(table_elems(s) * sizeof(double), total) : 1,
+    a.table_copies = get_copies(&r->d_more_tables, point && plan.copies ? copies(table_elems(s) * sizeof(double), total) : 1,
                                 table_elems(s), !scratch, st, rc_copies);
     a.image_copies = get_copies((ImgT **)&r->d_more_images, point ? 1 : copies(image_bytes(s), total),
                                 (size_t)s->image_elems, !scratch, st, rc_copies);
@@ -1165,12 +1120,7 @@ static int run_impl(mcrt_sim *s, uint64_t n_per_lambda, uint64_t first_id, uint6
     a.more_images = (ImgT *)r->d_more_images;
     a.image_elems = s->image_elems;
     a.tally = r->d_tally;
-    // (a wavelength's last chunk is a part, so there may be a few more of them
-    // than the waves they were made for)
-    a.own_chunks = G == kCartesian && a.n_chunks <= (uint64_t)s->ctx->n_cu * 12 &&
-                   (s->opt.waves_per_cu <= 0 || a.n_chunks <= waves);
-    if (waves > a.n_chunks || a.own_chunks) waves = a.n_chunks;
-    int grid = (int)((waves + (kBlock / 64) - 1) / (kBlock / 64));
+    int grid = (int)((plan.waves + (kBlock / 64) - 1) / (kBlock / 64));
     if (grid < 1) grid = 1;
 
     auto launch = [&]() -> hipError_t {
@@ -1785,7 +1735,7 @@ int mcrt_autotune(mcrt_sim *const *sims, int32_t n, const uint64_t *trial_packet
     // automatic chunk), so the search can only keep or beat them
     const mcrt_options &o0 = sims[0]->opt;
     const mcrt_tuning dflt{o0.chunk, o0.waves_per_cu > 0 ? o0.waves_per_cu : 16,
-                           o0.threshold > 0 ? o0.threshold : (n == 1 ? default_threshold(sims[0]) : 24), 0.0, 0, 0.0, o0.chunk_shift,
+                           o0.threshold > 0 ? o0.threshold : (n == 1 ? default_threshold(sims[0]->medium->grid->type == kOctree) : 24), 0.0, 0, 0.0, o0.chunk_shift,
                            o0.deposit_slots > 0 ? o0.deposit_slots : 16};
     mcrt_tuning cur = dflt;
     double ms = 0.0;
