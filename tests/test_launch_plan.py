@@ -50,3 +50,19 @@ def test_every_packet_has_a_wave(kind, octree):
             assert p["n_chunks"] == p["lam_chunks"] * n_lambda and 1 <= p["lanes"] <= 64
             assert 1 <= p["waves"] <= p["n_chunks"]
             assert p["waves"] == p["n_chunks"] or not p["own_chunks"]
+
+
+@pytest.mark.parametrize("count", [1, 200, 500, 5000, 32_769, 1_000_000])
+@pytest.mark.parametrize("tune", [dict(chunk=1), dict(chunk=16), dict(chunk=64), dict(chunk=256), dict(chunk=1024),
+                                  dict(chunk_shift=1), dict(chunk_shift=3), dict(chunk_shift=6),
+                                  dict(chunk=256, waves_per_cu=16), dict(chunk_shift=-2)])
+@pytest.mark.parametrize("kind", [dict(), dict(point=False), dict(octree=True), dict(direct=True)])
+def test_chunks_of_the_caller(kind, tune, count):
+    """A wave has a lane for every packet of a chunk, up to 64."""
+    p = plan(count, 2, **kind, **tune)
+    assert p["lanes"] >= min(64, p["chunk"])
+    if tune.get("chunk"):
+        assert p["chunk"] == tune["chunk"]
+    else:  # the automatic chunk's share of a shift does not change with the lanes
+        auto, shift = plan(count, 2, **kind)["chunk"], tune["chunk_shift"]
+        assert p["chunk"] == max(1, auto << shift if shift > 0 else auto >> -shift)
