@@ -306,8 +306,10 @@ int mcrt_sim_set_tuning(mcrt_sim *sim, const mcrt_tuning *t);
  * result is stored under a key describing the problem class (grid type,
  * precision, model count, cells, wavelengths, instruments) and reused on the
  * next call without trials.  The tuning is applied to every sim and returned
- * in *best.  Results do not depend on the tuning beyond the order of atomic
- * additions. */
+ * in *best.  Values that sims[0]'s options leave to each launch (0) and that no
+ * setting beats stay with the launch (and 0 in the cache); *best then has what
+ * the launch of trial_packets[0] made of them.  Results do not depend on the
+ * tuning beyond the order of atomic additions. */
 int mcrt_autotune(mcrt_sim *const *sims, int32_t n, const uint64_t *trial_packets, uint64_t seed,
                   const char *cache_path, mcrt_tuning *best);
 

@@ -21,6 +21,7 @@ struct LaunchIn {
 
 struct LaunchPlan {
     uint64_t waves;
+    int waves_per_cu;            // at most
     uint32_t chunk;              // packets per chunk
     uint64_t lam_chunks, n_chunks;
     int lanes;                   // lanes of a wave that take packets
@@ -46,8 +47,9 @@ inline LaunchPlan plan_launch(const LaunchIn &in)
 {
     LaunchPlan p{};
     const uint64_t total = in.count * in.n_lambda;
-    const uint64_t full = in.n_cu * (uint64_t)(in.waves_per_cu > 0 ? in.waves_per_cu : 16);
-    p.waves = full;
+    const int full_per_cu = in.waves_per_cu > 0 ? in.waves_per_cu : 16;
+    const uint64_t full = in.n_cu * (uint64_t)full_per_cu;
+    p.waves_per_cu = full_per_cu;
     // The queue's chunks: whole waves, eight or more chunks to a wave (the
     // tail: 1.6e6 packets of a depth-9 torus take 20.1 ms in chunks of 64, 25.9
     // in chunks of 192), at most 512 packets (1.6e7 packets of a 256^3 disk:
@@ -66,9 +68,10 @@ inline LaunchPlan plan_launch(const LaunchIn &in)
     // and 421; on the disk, 22 000 packets 1198, 1170 and 1202, in FP64 4000 for
     // each of 6 wavelengths 2076, 1890 and 2052).
     if (!in.octree && in.waves_per_cu <= 0) {
-        const uint64_t few = in.n_cu * (in.point && total <= in.n_cu * 8 * 32 ? 8 : 12);
-        if (total < 64 * few) p.waves = few;
+        const int few = in.point && total <= in.n_cu * 8 * 32 ? 8 : 12;
+        if (total < 64 * in.n_cu * few) p.waves_per_cu = few;
     }
+    p.waves = in.n_cu * (uint64_t)p.waves_per_cu;
     uint64_t lanes = (total + p.waves - 1) / p.waves;
     // A point source's direct light towards an instrument lands in one pixel,
     // in FP32 additions of one wave's share each, whose rounding follows their
@@ -91,6 +94,7 @@ inline LaunchPlan plan_launch(const LaunchIn &in)
     const bool queue = in.direct && !p.sums;
     if (queue) {
         lanes = 64;
+        p.waves_per_cu = full_per_cu;
         p.waves = full;
         auto_chunk = std::min<uint64_t>(256, std::max<uint64_t>(32, total / full));
         if (in.plain) {

@@ -919,6 +919,9 @@ int mcrt_result_zero(mcrt_result *res)
     return MCRT_OK;
 }
 
+// Whether s's results have sums of direct light.
+static bool sums_direct_light(const mcrt_sim *s) { return s->opt.precision == MCRT_FP32 && s->direct_light; }
+
 int mcrt_result_create(mcrt_sim *sim, mcrt_result **out)
 {
     if (!out) return fail(MCRT_EINVAL, "result_create: out is NULL");
@@ -933,7 +936,7 @@ int mcrt_result_create(mcrt_sim *sim, mcrt_result **out)
     // and for FP32 results of point sources the sums of direct light -- few
     // of those: 16 shards on lines of their own, for the packets of a launch
     // all start at once
-    const bool direct = sim->opt.precision == MCRT_FP32 && sim->direct_light;
+    const bool direct = sums_direct_light(sim);
     const size_t slots = direct ? (size_t)sim->n_ins * (size_t)sim->medium->n_lambda : 0;
     r->direct_shards = slots <= 1024 ? 16 : 1;
     r->direct_stride = slots <= 1024 ? 8 : 1;
@@ -1644,19 +1647,48 @@ int mcrt_batch_run_into(mcrt_sim *const *sims, int32_t n, const uint64_t *n_per_
     return batch_impl<double, double>(sims, n, n_per_lambda, seed, results);
 }
 
+// Sets s's tuning; waves_per_cu and threshold may be 0 (automatic) here.
+static bool apply_tuning(mcrt_sim *s, const mcrt_tuning &t)
+{
+    if (t.chunk < 0 || t.waves_per_cu < 0 || t.waves_per_cu > 32 || t.threshold < 0 || t.threshold > 64 ||
+        t.chunk_shift < -6 || t.chunk_shift > 6 || (t.deposit_slots != 0 && t.deposit_slots != 8 &&
+                                                     t.deposit_slots != 16))
+        return false;
+    s->opt.chunk = t.chunk;
+    s->opt.chunk_shift = t.chunk_shift;
+    s->opt.waves_per_cu = t.waves_per_cu;
+    s->opt.threshold = t.threshold;
+    s->opt.deposit_slots = t.deposit_slots;
+    return true;
+}
+
 int mcrt_sim_set_tuning(mcrt_sim *sim, const mcrt_tuning *t)
 {
     if (!sim || !t) return fail(MCRT_EINVAL, "sim_set_tuning: NULL argument");
-    if (t->chunk < 0 || t->waves_per_cu <= 0 || t->waves_per_cu > 32 || t->threshold <= 0 || t->threshold > 64 ||
-        t->chunk_shift < -6 || t->chunk_shift > 6 || (t->deposit_slots != 0 && t->deposit_slots != 8 &&
-                                                       t->deposit_slots != 16))
+    if (t->waves_per_cu == 0 || t->threshold == 0 || !apply_tuning(sim, *t))
         return fail(MCRT_EINVAL, "sim_set_tuning: values out of range");
-    sim->opt.chunk = t->chunk;
-    sim->opt.chunk_shift = t->chunk_shift;
-    sim->opt.waves_per_cu = t->waves_per_cu;
-    sim->opt.threshold = t->threshold;
-    sim->opt.deposit_slots = t->deposit_slots;
     return MCRT_OK;
+}
+
+// What a launch of the tuner (n sims, packets of the first) makes of t's
+// automatic values.
+static mcrt_tuning effective_tuning(const mcrt_sim *s, int32_t n, uint64_t packets, mcrt_tuning t)
+{
+    int waves = 16, threshold = 24; // a batch's
+    if (n == 1) {
+        LaunchIn in = launch_in(s, packets, s->source->type != kExpDisk, sums_direct_light(s), true);
+        in.chunk = t.chunk;
+        in.chunk_shift = t.chunk_shift;
+        in.waves_per_cu = t.waves_per_cu;
+        in.threshold = t.threshold;
+        const LaunchPlan plan = plan_launch(in);
+        waves = plan.waves_per_cu;
+        threshold = plan.threshold;
+    }
+    if (t.waves_per_cu == 0) t.waves_per_cu = waves;
+    if (t.threshold == 0) t.threshold = threshold;
+    if (t.deposit_slots == 0) t.deposit_slots = 16;
+    return t;
 }
 
 static std::string tune_key(mcrt_sim *const *sims, int32_t n)
@@ -1697,11 +1729,9 @@ int mcrt_autotune(mcrt_sim *const *sims, int32_t n, const uint64_t *trial_packet
                                                &t.deposit_slots) >= 4) {
                     std::fclose(f);
                     t.from_cache = 1;
-                    for (int i = 0; i < n; ++i) {
-                        int rc = mcrt_sim_set_tuning(sims[i], &t);
-                        if (rc) return rc;
-                    }
-                    *best = t;
+                    for (int i = 0; i < n; ++i)
+                        if (!apply_tuning(sims[i], t)) return fail(MCRT_EINVAL, "autotune: cached values out of range");
+                    *best = effective_tuning(sims[0], n, trial_packets[0], t);
                     return MCRT_OK;
                 }
             }
@@ -1720,10 +1750,7 @@ int mcrt_autotune(mcrt_sim *const *sims, int32_t n, const uint64_t *trial_packet
         }
     }
     auto trial = [&](const mcrt_tuning &t, double &ms) -> int {
-        for (int i = 0; i < n; ++i) {
-            int rc = mcrt_sim_set_tuning(sims[i], &t);
-            if (rc) return rc;
-        }
+        for (int i = 0; i < n; ++i) (void)apply_tuning(sims[i], t); // values of the search or of sims[0]
         int rc;
         if (n == 1) rc = mcrt_run_into(sims[0], trial_packets[0], 0, trial_packets[0], seed, res[0]);
         else rc = mcrt_batch_run_into(sims, n, trial_packets, seed, res.data());
@@ -1731,12 +1758,12 @@ int mcrt_autotune(mcrt_sim *const *sims, int32_t n, const uint64_t *trial_packet
         ms = res[0]->kernel_ms;
         return MCRT_OK;
     };
-    // start from the library's own defaults (sims[0]'s options; chunk 0 = the
-    // automatic chunk), so the search can only keep or beat them
+    // start from sims[0]'s options as they are, so that the search can only
+    // keep or beat them: what they leave to the launch (0) stays with it, in the
+    // trials and afterwards, until a setting wins (a launch of 5000 packets in a
+    // 32^3 sphere: 0.34 ms as it chooses, 0.37 with 16 waves per compute unit set)
     const mcrt_options &o0 = sims[0]->opt;
-    const mcrt_tuning dflt{o0.chunk, o0.waves_per_cu > 0 ? o0.waves_per_cu : 16,
-                           o0.threshold > 0 ? o0.threshold : (n == 1 ? default_threshold(sims[0]->medium->grid->type == kOctree) : 24), 0.0, 0, 0.0, o0.chunk_shift,
-                           o0.deposit_slots > 0 ? o0.deposit_slots : 16};
+    const mcrt_tuning dflt{o0.chunk, o0.waves_per_cu, o0.threshold, 0.0, 0, 0.0, o0.chunk_shift, o0.deposit_slots};
     mcrt_tuning cur = dflt;
     double ms = 0.0;
     int rc = trial(cur, ms); // warm-up
@@ -1753,7 +1780,9 @@ int mcrt_autotune(mcrt_sim *const *sims, int32_t n, const uint64_t *trial_packet
     const int waves[] = {8, 12, 16};
     const int slots[] = {8, 16}; // the batch kernel's deposit tile (FP32 batches only)
     const int passes = n > 1 && o0.precision == MCRT_FP32 ? 4 : 3;
-    auto same = [](const mcrt_tuning &x, const mcrt_tuning &y) {
+    auto same = [&](const mcrt_tuning &a, const mcrt_tuning &b) {
+        const mcrt_tuning x = effective_tuning(sims[0], n, trial_packets[0], a),
+                          y = effective_tuning(sims[0], n, trial_packets[0], b);
         return x.chunk == y.chunk && x.chunk_shift == y.chunk_shift && x.threshold == y.threshold &&
                x.waves_per_cu == y.waves_per_cu && x.deposit_slots == y.deposit_slots;
     };
@@ -1772,6 +1801,13 @@ int mcrt_autotune(mcrt_sim *const *sims, int32_t n, const uint64_t *trial_packet
             } else {
                 t.deposit_slots = vals[k];
             }
+            // a value that the launch takes by itself is left to it
+            mcrt_tuning own = t;
+            own.waves_per_cu = own.threshold = own.deposit_slots = 0;
+            own = effective_tuning(sims[0], n, trial_packets[0], own);
+            if (dflt.waves_per_cu == 0 && t.waves_per_cu == own.waves_per_cu) t.waves_per_cu = 0;
+            if (dflt.threshold == 0 && t.threshold == own.threshold) t.threshold = 0;
+            if (dflt.deposit_slots == 0 && t.deposit_slots == own.deposit_slots) t.deposit_slots = 0;
             if (same(t, cur)) continue;
             rc = trial(t, ms);
             if (rc) break;
@@ -1807,12 +1843,9 @@ int mcrt_autotune(mcrt_sim *const *sims, int32_t n, const uint64_t *trial_packet
     }
     cleanup();
     if (rc) return rc;
-    for (int i = 0; i < n; ++i) {
-        rc = mcrt_sim_set_tuning(sims[i], &cur);
-        if (rc) return rc;
-    }
+    for (int i = 0; i < n; ++i) (void)apply_tuning(sims[i], cur);
     cur.from_cache = 0;
-    *best = cur;
+    *best = effective_tuning(sims[0], n, trial_packets[0], cur);
     if (cache_path) {
         std::FILE *f = std::fopen(cache_path, "a");
         if (f) {
