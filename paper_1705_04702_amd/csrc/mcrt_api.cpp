@@ -1001,7 +1001,7 @@ template <typename T>
 static int get_copies(T **p, int n, size_t elems, bool may_alloc, hipStream_t st, int &rc)
 {
     if (n > 1 && !*p && may_alloc) {
-        const size_t bytes = 7 * elems * sizeof(T); // as many as any launch takes
+        const size_t bytes = (size_t)(n - 1) * elems * sizeof(T); // n is 1 or this in every launch (see copies)
         void *q = nullptr;
         if (dev_alloc(&q, bytes) == MCRT_OK) {
             const hipError_t e = launch_fill_zero(q, bytes, st);
