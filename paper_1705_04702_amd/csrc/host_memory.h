@@ -24,10 +24,35 @@ namespace mcrt {
 
 // Device blocks of one context that are free to be used again.  All work of a
 // context runs on its one stream, so a block's next user is ordered behind its
-// last.  Kept up to kIdleBytes; freed with the context, or when the device has
-// no memory for a new block.
+// last.  Kept up to kIdleBytes; freed with the context, or when any allocation of
+// the library finds no memory left on the device.
 class DevicePool {
   public:
+    static std::shared_ptr<DevicePool> make(int device)
+    {
+        auto pool = std::make_shared<DevicePool>(device);
+        All &all = every();
+        std::lock_guard<std::mutex> lock(all.mu);
+        all.pools.erase(std::remove_if(all.pools.begin(), all.pools.end(),
+                                       [](const std::weak_ptr<DevicePool> &w) { return w.expired(); }),
+                        all.pools.end());
+        all.pools.push_back(pool);
+        return pool;
+    }
+
+    // Memory of the current device, `device`: where it has none left, the idle
+    // blocks of all contexts on it are freed first.
+    static hipError_t allocate(int device, void **p, size_t bytes)
+    {
+        hipError_t e = hipMalloc(p, bytes);
+        if (e != hipSuccess && drain_all(device)) {
+            (void)hipGetLastError();
+            e = hipMalloc(p, bytes);
+        }
+        if (e != hipSuccess) *p = nullptr;
+        return e;
+    }
+
     explicit DevicePool(int device) : device_(device) { idle_.reserve(kIdleBlocks); }
     ~DevicePool() { close(); }
     DevicePool(const DevicePool &) = delete;
@@ -55,14 +80,8 @@ class DevicePool {
                 return hipSuccess;
             }
         }
-        hipError_t e = hipMalloc(p, bytes);
-        if (e != hipSuccess && drain()) {
-            (void)hipGetLastError();
-            e = hipMalloc(p, bytes);
-        }
-        if (e != hipSuccess) *p = nullptr;
         *cap = bytes;
-        return e;
+        return allocate(device_, p, bytes);
     }
 
     void put(void *p, size_t cap)
@@ -94,6 +113,31 @@ class DevicePool {
         size_t cap;
     };
     static constexpr size_t kIdleBlocks = 32, kIdleBytes = size_t(1) << 30;
+
+    struct All {
+        std::mutex mu;
+        std::vector<std::weak_ptr<DevicePool>> pools;
+    };
+    static All &every()
+    {
+        static All *all = new All; // outlives any context
+        return *all;
+    }
+
+    static bool drain_all(int device)
+    {
+        std::vector<std::shared_ptr<DevicePool>> pools;
+        {
+            All &all = every();
+            std::lock_guard<std::mutex> lock(all.mu);
+            for (const std::weak_ptr<DevicePool> &w : all.pools)
+                if (std::shared_ptr<DevicePool> pool = w.lock())
+                    if (pool->device_ == device) pools.push_back(std::move(pool));
+        }
+        bool any = false;
+        for (const std::shared_ptr<DevicePool> &pool : pools) any = pool->drain() || any;
+        return any;
+    }
 
     bool drain()
     {

@@ -53,9 +53,10 @@ int dev_alloc(void **p, size_t bytes)
     *p = nullptr;
     if (debug_fail_alloc()) return fail(MCRT_ENOMEM, "device allocation refused (MCRT_DEBUG_FAIL_ALLOC=1)");
     if (bytes == 0) bytes = 16;
-    hipError_t e = hipMalloc(p, bytes);
+    int device = 0;
+    hipError_t e = hipGetDevice(&device);
+    if (e == hipSuccess) e = DevicePool::allocate(device, p, bytes);
     if (e != hipSuccess) {
-        *p = nullptr;
         (void)hipGetLastError();
         return fail(MCRT_ENOMEM, "hipMalloc of " + std::to_string(bytes) + " bytes failed: " + hipGetErrorString(e));
     }
@@ -509,7 +510,7 @@ int mcrt_context_create(int device, void *stream, mcrt_context **out)
     int ncu = 0;
     HIP_TRY(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, device));
     auto *c = new mcrt_context;
-    c->pool = std::make_shared<DevicePool>(device);
+    c->pool = DevicePool::make(device);
     c->staging = Staging::of(device);
     c->device = device;
     c->stream = (hipStream_t)stream;
