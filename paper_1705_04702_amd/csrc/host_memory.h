@@ -306,6 +306,19 @@ class Staging {
     hipEvent_t events_[kSlots] = {};
 };
 
+// Whether p is ordinary host memory, which the runtime does not know.  Memory that
+// it allocated for the host may still be the target of a copy on a stream, so a
+// copy from it has its place on the stream, and the host does not read it before.
+inline bool ordinary(const void *p)
+{
+    hipPointerAttribute_t a{};
+    if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return a.type == hipMemoryTypeUnregistered;
+}
+
 // Whether p is memory that only the host uses (the runtime does not know it)
 // or that was allocated as host memory.
 inline bool on_host(const void *p)

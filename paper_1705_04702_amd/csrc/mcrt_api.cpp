@@ -184,7 +184,7 @@ hipError_t copy_in(const mcrt_context *c, void *dst, const void *src, size_t byt
 {
     bool done = false;
     hipError_t e = hipSuccess;
-    if (bytes >= kLargeBytes && staging(c) && on_host(src)) e = staging(c)->upload(dst, src, bytes, c->stream, done);
+    if (bytes >= kLargeBytes && staging(c) && ordinary(src)) e = staging(c)->upload(dst, src, bytes, c->stream, done);
     if (done || e != hipSuccess) return e;
     return hipMemcpyAsync(dst, src, bytes, hipMemcpyDefault, c->stream);
 }
@@ -2269,7 +2269,7 @@ int mcrt_proposal_grad(mcrt_proposal *p, const float *X, const float *KP, const 
     HIP_TRY(hipSetDevice(p->ctx->device));
     hipStream_t st = p->ctx->stream;
     std::vector<float> hc;
-    if (!on_host(C)) {
+    if (!ordinary(C)) {
         hc.resize((size_t)n);
         HIP_TRY(hipMemcpy(hc.data(), C, (size_t)n * sizeof(float), hipMemcpyDefault));
     }
