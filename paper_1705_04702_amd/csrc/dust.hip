@@ -248,6 +248,18 @@ hipError_t launch_dust_scan(double *x, long long n, int rows, double *tile_sums,
     return hipGetLastError();
 }
 
+__global__ void totals_kernel(const double *cdf, long long n, int rows, double *total)
+{
+    const int r = blockIdx.x * blockDim.x + threadIdx.x;
+    if (r < rows) total[r] = cdf[r * n + n - 1];
+}
+
+hipError_t launch_dust_totals(const double *cdf, long long n, int rows, double *total, hipStream_t st)
+{
+    hipLaunchKernelGGL(totals_kernel, dim3((rows + 63) / 64), dim3(64), 0, st, cdf, n, rows, total);
+    return hipGetLastError();
+}
+
 hipError_t launch_dust_guide(const double *cdf, long long n, int K, int rows, int *guide, hipStream_t st)
 {
     const long long total = (long long)K * rows;

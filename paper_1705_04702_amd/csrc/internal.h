@@ -117,6 +117,8 @@ hipError_t launch_dust_emission(const DustGrid &g, const double *absorbed, const
                                 double *T, double *emis, hipStream_t st);
 // x[rows][n] := inclusive running sums of each row; tile_sums[rows][tiles]
 hipError_t launch_dust_scan(double *x, long long n, int rows, double *tile_sums, hipStream_t st);
+// total[rows]: the last running sum of each row
+hipError_t launch_dust_totals(const double *cdf, long long n, int rows, double *total, hipStream_t st);
 // guide[rows][K]: first index whose running sum exceeds k (row total / K)
 hipError_t launch_dust_guide(const double *cdf, long long n, int K, int rows, int *guide, hipStream_t st);
 

@@ -1377,10 +1377,13 @@ int mcrt_dust_create(mcrt_sim *sim, const mcrt_result *const *absorbed, int32_t 
         if (e == hipSuccess) e = launch_dust_scan(d->d_cdf, nc, nl, d_tiles, st);
         if (e == hipSuccess) e = launch_dust_guide(d->d_cdf, nc, d->K, nl, d->d_guide, st);
         d->L.assign((size_t)nl, 0.0);
-        if (e == hipSuccess) // the last running sum of every wavelength
-            e = hipMemcpy2DAsync(d->L.data(), sizeof(double), d->d_cdf + (nc - 1), (size_t)nc * sizeof(double),
-                                 sizeof(double), (size_t)nl, hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        // the last running sum of every wavelength, gathered by a kernel: a strided
+        // copy of the runtime's into ordinary memory returns without an error and
+        // without the data where a profiler records the process
+        if (e == hipSuccess) e = launch_dust_totals(d->d_cdf, nc, nl, d_lam, st);
+        if (e == hipSuccess)
+            e = (size_t)nl * sizeof(double) <= kSmallBytes ? read_words(sim->ctx, d->L.data(), d_lam, (size_t)nl)
+                                                           : copy_out(sim->ctx, d->L.data(), d_lam, (size_t)nl * sizeof(double));
     }
     if (!rc && e != hipSuccess) rc = fail(MCRT_EDEVICE, std::string("dust_create: ") + hipGetErrorString(e));
     if (rc) {
