@@ -36,7 +36,7 @@ template <typename Real, typename ImgT, int G> struct TransportArgs {
     // and not from the queue, whose counter is one line for all waves (8000
     // packets in a 32^3 sphere: 567 -> 527 us)
     int own_chunks;
-    int mixed;                    // march all kinds in one loop (see transport_kernel.h)
+    int mixed;                    // march all kinds in one loop (see launch_plan.h)
     unsigned long long *counter;  // queue position (chunks handed out)
     // further copies of the table, [table_copies - 1][n_lambda][n_store], and
     // of the images; workgroup b adds to copy b mod their (power-of-two) number

@@ -84,11 +84,12 @@ inline LaunchPlan plan_launch(const LaunchIn &in)
     // for copies of it change which lanes are free together.  Any other shape
     // rounds otherwise, and to more: image against 64 bits in that sphere, mean of
     // 12 seeds, 60 000 packets 1.2e-5 so, 1.4e-5 in chunks that waves own, marching
-    // apart (0.73 and 0.52 ms); 1e5 packets 1.5e-5 in any shape on average, but 0.7
+    // apart (0.73 and 0.52 ms); 1e5 packets 1.5e-5 in any shape on average, but 0.8
     // and 1.1e-5 at one seed (0.97 and 0.78 ms); 2e5 packets 3.6 to 4.7e-4 so, 5.8e-4
     // with copies (1.97 and 1.65 ms).  FP64 sums would be exact to 1e-6 at every
     // size, but move images by the whole of these errors, which is more than a
-    // change of the launch may move them.
+    // change of the launch may move them.  (Learned runs and histories have no mixed
+    // loop: 1.5e-5 of 1e5 packets, 2.4e-5 of 2e5, where full waves refill at once.)
     p.sums = in.direct && in.count <= 32768;
     p.copies = true;
     const bool queue = in.direct && !p.sums;

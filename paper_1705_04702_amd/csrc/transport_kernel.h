@@ -20,9 +20,11 @@
 // kind's instructions in each iteration, and the event code, which costs as
 // much as several iterations, for each few lanes that finish.  With the kinds
 // apart it pays to wait for all lanes (threshold 64) on Cartesian grids and
-// for 48 on octrees, whose longest rays are further from the mean: 1e6 packets
-// in a 32^3 sphere 11.9 -> 5.9 ms, 1.6e6 in a depth-7 torus 22.4 -> 16.8 ms
-// (mixed kinds at 16 lanes, against 64 / 48).
+// for 48 on octrees, whose longest rays are further from the mean: 1.6e6
+// packets in a depth-7 torus 22.4 -> 16.8 ms, with copies of the table (see
+// transport_body) 1e6 in a 32^3 sphere in FP64 13.8 -> 7.2 ms (mixed kinds at 16
+// lanes, against 48 and 64).  FP32 launches that add direct light to their images
+// packet by packet keep the mixed loop (see launch_plan.h).
 // The last packets are the longest: once the queue is empty a wave leaves the
 // propagation loop only when all its lanes have finished, and a launch that
 // cannot fill every wave spreads its packets over all of them, `lanes` to a
@@ -299,7 +301,7 @@ __device__ __forceinline__ double push_value(double x, int to)
 //     multiplied or summed through lane by lane, in the order of the cells.
 // Every value is computed by the operations of march_batch, so deposits,
 // interaction points and depths are bit for bit the same.  Kernel of 500 packets
-// in a 32^3 sphere 285 -> 227 us, of 220 on a 61 x 45 x 27 disk 830 -> 665 us (what
+// in a 32^3 sphere 285 -> 222 us, of 220 on a 61 x 45 x 27 disk 830 -> 620 us (what
 // remains is the events, about 2500 vector instructions each); with more than one
 // packet to a wave, marched one after another, nothing is gained (4000 in the
 // sphere, two to a wave: 316 and 327 us), and 1e5 there lose 5 % to the registers.
@@ -541,8 +543,8 @@ __device__ __forceinline__ void transport_body()
     // source), of small images for extended ones (all packets share the
     // pixels).  Workgroups are placed round-robin over the XCDs, so eight
     // copies give each XCD its own.  1.6e6 packets in a depth-7 torus, 8
-    // wavelengths: 17.3 ms with one table, 12.8 with eight; 1e6 in a 32^3
-    // sphere: 5.8 and 4.5; disks gain nothing from copies of their tables.
+    // wavelengths: 17.3 ms with one table, 12.8 with eight; disks gain nothing
+    // from copies of their tables.
     // 2.2e6 packets of a 61 x 45 x 27 disk, 11 wavelengths, three 33^2 images:
     // 18.5 ms in chunks of 64 with one set of images, 8.6 with eight.
     double *table = a.view.table;
@@ -750,8 +752,10 @@ __global__ void __launch_bounds__(kBlock) transport_kernel_f64(TransportArgs<dou
 // (942 000 packets of 48 models 34.6 -> 29.7 ms; 16.5e6 of 64 models 385 mixed,
 // 395 to 420 so).  Models of at most 3072 packets per wavelength, whose images
 // differ by less than 1e-5 between any two orders of their additions, march apart
-// from the start, in chunks that spread the batch over the chip (126 000 packets of
-// 48 models 20.4 -> 12.8 ms).
+// from the start, in chunks that spread the batch over the chip, as far as waves
+// take them in turn (126 000 packets of 48 models 20.4 -> 12.8 ms).  These chunks,
+// 64 packets at most, pay as well where the batch has too many for this kernel
+// (256 models of 3000 packets 19.0 -> 11.0 ms, 1000 of them 37.4 -> 31.0).
 template <typename Real, typename ImgT, int SLOTS, bool DRAIN>
 __device__ __forceinline__ void batch_body(const BatchArgs<Real, ImgT> &a,
                                            const ModelDesc<Real, ImgT> *__restrict__ models)
@@ -911,9 +915,10 @@ __global__ void __launch_bounds__(kBlock) batch_transport_kernel_f64(BatchArgs<d
 }
 
 // After an FP32 launch: its sums of direct light join their pixels and are
-// cleared for the next launch.  One rounding per pixel, where thousands of
-// small FP32 additions of equal size to one pixel all round the same way
-// (up to 3e-4 of the pixel in launches of 5e4 packets).
+// cleared for the next launch.  A wave's share is a tree of FP32 additions over
+// its lanes (six roundings at most), the pixel one more, where thousands of FP32
+// additions of equal size to one pixel all round the same way (32^3 sphere: up
+// to 2.5e-5 of the pixel in launches of 6e4 packets, 1e-3 in 2e5).
 template <typename ImgT> __global__ void __launch_bounds__(64) direct_kernel(View<float, ImgT, 0> v)
 {
     const int slots = v.n_ins * v.n_lambda;
