@@ -99,7 +99,7 @@ hipError_t launch_proposal_forward(const uint16_t *frags, const float *bias, con
 // ---------------------------------------------------------------------------
 // Loss gradient of one sample with respect to the 40 network outputs o, by
 // the four lanes l, l + 16, l + 32, l + 48 of a wave: lane part p = lane / 16
-// takes lobes 2p and 2p + 1.  Returns w * (-log q_vMF(kp)) (in every lane);
+// takes lobes 2p and 2p + 1.  Returns log q_vMF(kp) (in every lane);
 // dl, da, dk: d(w * -log q) / d of its lobes' logits, axes and concentrations.
 // Sums over lobes run in lobe order in every lane.
 // ---------------------------------------------------------------------------
@@ -158,7 +158,7 @@ __device__ __forceinline__ float nll_grad2(const float *o, const float kp[3], fl
         const float dlogf = 1.0f / kap[h] - 2.0f * e2 / (-expm1f(-2.0f * kap[h])) + (dot[h] - 1.0f);
         dk[h] = -w * r * dlogf * dkds[h];
     }
-    return -w * logf(q);
+    return logf(q);
 }
 
 // ---------------------------------------------------------------------------
@@ -226,7 +226,7 @@ __global__ void __launch_bounds__(256) grad_kernel(GradArgs g)
     __shared__ __attribute__((aligned(16))) uint16_t s_dz2[2][64 * kSX];
     __shared__ __attribute__((aligned(16))) uint16_t s_dz1[2][64 * kSX];
     __shared__ float s_db[2][4][64];                                    // the waves' sums of dZ1, dZ2
-    __shared__ float s_nll[64];
+    __shared__ float2 s_nll[64]; // weight and negative log-likelihood by sample
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     {
@@ -289,8 +289,8 @@ __global__ void __launch_bounds__(256) grad_kernel(GradArgs g)
         // ---- loss gradient: four lanes to a sample ----
         {
             float dl[2], da[2][3], dk[2];
-            const float nll = nll_grad2(s_stage + mine * 41, kp, w, lane, dl, da, dk);
-            if (p == 0) s_nll[mine] = valid ? nll : 0.0f;
+            const float lq = nll_grad2(s_stage + mine * 41, kp, w, lane, dl, da, dk);
+            if (p == 0) s_nll[mine] = valid ? make_float2(w, -lq) : make_float2(0.0f, 0.0f);
             wave_lds_sync(); // all lanes have read the outputs
 #pragma unroll
             for (int h = 0; h < 2; ++h)
@@ -384,7 +384,7 @@ __global__ void __launch_bounds__(256) grad_kernel(GradArgs g)
                 for (int s = 0; s < 64; ++s) sacc += s_stage[s * 41 + lane];
             db3 += sacc;
         } else if (wave == 2) {
-            loss += s_nll[lane];
+            loss = fmaf(s_nll[lane].x, s_nll[lane].y, loss); // one rounding for product and sum
         }
         // ---- weight gradients: hidden rows 16 wave .. of dW3 += H2^T dO and
         //      dW2 += H1^T dZ2, hidden columns 16 wave .. of dW1 += X^T dZ1 ----
