@@ -31,6 +31,7 @@ template <typename Real, typename ImgT, int G> struct TransportArgs {
     uint32_t chunk;               // packets per chunk (all of one wavelength)
     int threshold;                // lanes that must finish their propagation before events run
     int lanes;                    // lanes of a wave that take packets (64 but in small launches)
+    int lone;                     // one lane, whose packets the whole wave marches (see lone_march)
     // no more chunks than waves, all resident: a wave takes the chunk of its
     // number (neighbouring chunks, of like cost, on different compute units),
     // and not from the queue, whose counter is one line for all waves (8000

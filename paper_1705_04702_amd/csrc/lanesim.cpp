@@ -258,12 +258,12 @@ extern "C" int ls_run(const ls_scene *s, uint64_t n_per_lambda, uint64_t first_i
 }
 
 // The launch rules (launch_plan.h): in the fields of LaunchIn, out those of LaunchPlan.
-extern "C" void ls_plan(const int64_t in[11], int64_t out[10])
+extern "C" void ls_plan(const int64_t in[12], int64_t out[11])
 {
-    const LaunchIn x{(uint64_t)in[0], (uint64_t)in[1], (uint64_t)in[2], in[3] != 0, in[4] != 0, in[5] != 0, in[6] != 0,
-                     (int)in[7], (int)in[8], (int)in[9], (int)in[10]};
+    const LaunchIn x{(uint64_t)in[0], (uint64_t)in[1], (uint64_t)in[2], (uint64_t)in[11], in[3] != 0, in[4] != 0,
+                     in[5] != 0, in[6] != 0, (int)in[7], (int)in[8], (int)in[9], (int)in[10]};
     const LaunchPlan p = plan_launch(x);
-    const int64_t y[10] = {(int64_t)p.waves, p.chunk, (int64_t)p.lam_chunks, (int64_t)p.n_chunks, p.lanes, p.threshold,
-                          p.mixed, p.sums, p.own_chunks, p.copies};
-    for (int i = 0; i < 10; ++i) out[i] = y[i];
+    const int64_t y[11] = {(int64_t)p.waves, p.chunk, (int64_t)p.lam_chunks, (int64_t)p.n_chunks, p.lanes, p.threshold,
+                          p.mixed, p.sums, p.own_chunks, p.copies, p.lone};
+    for (int i = 0; i < 11; ++i) out[i] = y[i];
 }

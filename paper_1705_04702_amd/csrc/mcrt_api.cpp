@@ -967,8 +967,10 @@ int mcrt_result_create(mcrt_sim *sim, mcrt_result **out)
 // What the launch rules look at, for count packets per wavelength of s.
 static LaunchIn launch_in(const mcrt_sim *s, uint64_t count, bool point, bool direct, bool no_hist)
 {
-    return {(uint64_t)s->ctx->n_cu, count, (uint64_t)s->medium->n_lambda, s->medium->grid->type == kOctree, point,
-            direct, !s->prop && no_hist, s->opt.chunk, s->opt.chunk_shift, s->opt.waves_per_cu, s->opt.threshold};
+    const mcrt_grid *g = s->medium->grid;
+    return {(uint64_t)s->ctx->n_cu, count, (uint64_t)s->medium->n_lambda,
+            (uint64_t)g->n[0] + (uint64_t)g->n[1] + (uint64_t)g->n[2], g->type == kOctree, point, direct,
+            !s->prop && no_hist, s->opt.chunk, s->opt.chunk_shift, s->opt.waves_per_cu, s->opt.threshold};
 }
 
 // The launch sums its direct light in r's FP64 sums.
@@ -1108,6 +1110,7 @@ static int run_impl(mcrt_sim *s, uint64_t n_per_lambda, uint64_t first_id, uint6
     if (plan.sums) set_direct(v, s, r);
     a.threshold = plan.threshold;
     a.lanes = plan.lanes;
+    a.lone = plan.lone;
     a.chunk = plan.chunk;
     a.lam_chunks = plan.lam_chunks;
     a.n_chunks = plan.n_chunks;

@@ -305,6 +305,7 @@ __device__ __forceinline__ double push_value(double x, int to)
 // remains is the events, about 2500 vector instructions each); with more than one
 // packet to a wave, marched one after another, nothing is gained (4000 in the
 // sphere, two to a wave: 316 and 327 us), and 1e5 there lose 5 % to the registers.
+// Nor on grids of a few cells (see launch_plan.h).
 // PROP: a propagation, else a search or a peel-off.  Whole wave active.
 // A march that cannot go on this way (no finite crossing) stays with lane 0.
 template <bool PROP, typename Real, typename ImgT, int G>
@@ -954,7 +955,7 @@ hipError_t launch_transport_impl(const TransportArgs<Real, ImgT, G> &a, int grid
             hipLaunchKernelGGL((transport_kernel_f32<G, false, true, false>), dim3(grid), dim3(kBlock), 0, stream, a);
         else if (a.mixed)
             hipLaunchKernelGGL((transport_kernel_f32<G, false, false, true>), dim3(grid), dim3(kBlock), 0, stream, a);
-        else if (G == kCartesian && a.lanes == 1)
+        else if (G == kCartesian && a.lone)
             hipLaunchKernelGGL((transport_kernel_f32<G, false, false, false, G == kCartesian>), dim3(grid), dim3(kBlock), 0, stream, a);
         else
             hipLaunchKernelGGL((transport_kernel_f32<G, false, false, false>), dim3(grid), dim3(kBlock), 0, stream, a);
@@ -975,7 +976,7 @@ hipError_t launch_transport_impl(const TransportArgs<Real, ImgT, G> &a, int grid
             hipLaunchKernelGGL((transport_kernel_f64<G, true, false>), dim3(grid), dim3(kBlock), 0, stream, a);
         else if (a.view.hist)
             hipLaunchKernelGGL((transport_kernel_f64<G, false, true>), dim3(grid), dim3(kBlock), 0, stream, a);
-        else if (G == kCartesian && a.lanes == 1)
+        else if (G == kCartesian && a.lone)
             hipLaunchKernelGGL((transport_kernel_f64<G, false, false, G == kCartesian>), dim3(grid), dim3(kBlock), 0, stream, a);
         else
             hipLaunchKernelGGL((transport_kernel_f64<G, false, false>), dim3(grid), dim3(kBlock), 0, stream, a);

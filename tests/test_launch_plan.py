@@ -6,14 +6,14 @@ import pytest
 
 import lanesim
 
-FIELDS = ("waves", "chunk", "lam_chunks", "n_chunks", "lanes", "threshold", "mixed", "sums", "own_chunks", "copies")
+FIELDS = ("waves", "chunk", "lam_chunks", "n_chunks", "lanes", "threshold", "mixed", "sums", "own_chunks", "copies", "lone")
 
 
 def plan(count, n_lambda=1, octree=False, point=True, direct=False, plain=True, chunk=0, chunk_shift=0, waves_per_cu=0,
-         threshold=0, n_cu=256):
-    a = (ctypes.c_int64 * 11)(n_cu, count, n_lambda, octree, point, direct, plain, chunk, chunk_shift, waves_per_cu,
-                              threshold)
-    out = (ctypes.c_int64 * 10)()
+         threshold=0, n_cu=256, cells=96):
+    a = (ctypes.c_int64 * 12)(n_cu, count, n_lambda, octree, point, direct, plain, chunk, chunk_shift, waves_per_cu,
+                              threshold, cells)
+    out = (ctypes.c_int64 * 11)()
     lanesim.lib().ls_plan(a, out)
     return dict(zip(FIELDS, out))
 
@@ -66,3 +66,13 @@ def test_chunks_of_the_caller(kind, tune, count):
     else:  # the automatic chunk's share of a shift does not change with the lanes
         auto, shift = plan(count, 2, **kind)["chunk"], tune["chunk_shift"]
         assert p["chunk"] == max(1, auto << shift if shift > 0 else auto >> -shift)
+
+
+@pytest.mark.parametrize("count", [1, 500, 2048, 2049, 3072, 3073, 5000])
+@pytest.mark.parametrize("cells", [3, 18, 29, 30, 300])
+def test_lone_packets(cells, count):
+    """The whole wave marches a packet where it has only one and rays are long."""
+    for kind in (dict(), dict(point=False), dict(direct=True), dict(octree=True), dict(plain=False), dict(chunk=2)):
+        p = plan(count, cells=cells, **kind)
+        assert p["lone"] == (p["lanes"] == 1 and cells >= 30 and not kind.get("octree") and kind.get("plain", True))
+    assert plan(count, cells=cells)["lanes"] == max(1, -(-count // 2048))
