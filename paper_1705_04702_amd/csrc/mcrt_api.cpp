@@ -171,7 +171,7 @@ hipError_t copy_out(const mcrt_context *c, void *dst, const void *src, size_t by
 {
     bool done = false;
     hipError_t e = hipSuccess;
-    if (bytes >= kLargeBytes && staging(c) && on_host(dst))
+    if (bytes >= kLargeBytes && staging(c) && ordinary(dst))
         e = to_host_with(c, (char *)dst, (const char *)src, bytes, done,
                          [](char *d, const char *s, size_t k) { std::memcpy(d, s, k); });
     if (done || e != hipSuccess) return e;
@@ -1948,7 +1948,7 @@ static hipError_t image_out(const mcrt_context *c, const ImgT *src, int64_t n, d
             if (e == hipSuccess) std::memcpy(out, cell.data(), bytes);
             return e;
         }
-    } else if (host && bytes >= kImageBytes && staging(c)) {
+    } else if (host && bytes >= kImageBytes && staging(c) && ordinary(out)) {
         bool done = false;
         e = to_host_with(c, out, src, (size_t)n, done, [scale](double *d, const ImgT *s, size_t k) {
             for (size_t i = 0; i < k; ++i) d[i] = (double)s[i] * scale;
